@@ -155,7 +155,7 @@ typedef struct {
   int32_t pad_;
   int64_t n_fwd_local, n_fwd_recv, n_fwd_fused, n_bwd; /* work items */
   int64_t pairs_loc, pairs_recv; /* visible (query, key) pairs per head */
-  int64_t meta_bytes;           /* device bytes fc_view_bind needs */
+  int64_t meta_bytes;           /* device bytes fc_view_bind takes */
   int64_t n_bwd_launch;         /* backward launch items after splitting long */
   int64_t n_bwd_reduce;         /*   key tiles; key tiles split; partial slots */
   int64_t n_bwd_slots;
@@ -221,14 +221,43 @@ int fc_view_export_launch(fc_view view, int32_t* fwd_local, int32_t* fwd_recv,
                           int32_t* fwd_fused, int32_t* bwd_launch, int32_t* bwd_reduce,
                           int32_t* bwd_qfirst);
 
+/* The tables of a view whose long key ranges are split over workgroups (few
+ * workgroups, or one much longer than the others; for checks). counts (never
+ * NULL) receives the forward's chunk length in key tiles (0: the forward is
+ * not split), then the row counts of the four tables; the tables (any may be
+ * NULL) have 8 int32 per row:
+ *   dq_items   dQ work items of fc_attn_bwd_pass: a forward item's fields
+ *              (q0, q1, r0, r1, l0, l1, ldiag) over part of its key tiles,
+ *              then the partial slot (-1: all of them); empty if no dQ range
+ *              is split;
+ *   dq_comb    (q0, q1, first slot, slot count, 0, 0, 0, 0) per split tile;
+ *   fwd_units  the forward's chunks: forward item fields over one chunk of one
+ *              source, then the partial slot;
+ *   fwd_comb   (q0, q1, first slot, received chunks, local chunks, 0, 0, 0)
+ *              per query tile, its slots in key order, received first. */
+int fc_view_export_split(fc_view view, int32_t counts[5], int32_t* dq_items, int32_t* dq_comb,
+                         int32_t* fwd_units, int32_t* fwd_comb);
+
 /* Upload the view's tables into `dev_meta` (device, >= meta_bytes, 256-byte
- * aligned) on `stream` and remember that buffer for later kernel calls. */
+ * aligned) on `stream` and remember that buffer for later kernel calls. Where
+ * the forward is split, meta_bytes covers the chunks' partial slots (the size
+ * of fc_workspace_size) behind the tables: the partial passes, which take no
+ * workspace, write them. Calls on several streams or threads are ordered by
+ * the library (the local and the received pass use slots of their own). A
+ * buffer that holds the tables alone is accepted too: the partial passes then
+ * run each query tile's chunks in one workgroup, as they do while a stream is
+ * captured; the results are the same. */
 int fc_view_bind(fc_view view, void* dev_meta, size_t bytes, void* stream);
 
 void fc_view_destroy(fc_view view);
 
 /* Workspace bytes fc_attn_fwd (for `mode`), fc_attn_bwd and, alone,
- * fc_attn_bwd_dkdv / fc_attn_bwd_pass need (any pointer may be NULL). */
+ * fc_attn_bwd_dkdv / fc_attn_bwd_pass need (any pointer may be NULL). Two
+ * calls also run with less, without splitting query tiles' key ranges (the
+ * results then differ in their last bits): fc_attn_fwd with no workspace where
+ * one pass suffices (FC_FUSED, or a view that receives nothing), and
+ * fc_attn_bwd_dkdv / fc_attn_bwd_pass with a workspace that holds the partial
+ * dK/dV of split key tiles alone. */
 int fc_workspace_size(fc_view view, int32_t mode, size_t* fwd_bytes, size_t* bwd_bytes,
                       size_t* dkdv_bytes);
 
@@ -249,7 +278,11 @@ int fc_kv_gather(fc_view view, const void* k_packed, const void* v_packed, int64
  * query tile's received partial O goes to the workspace and is merged with
  * its local partial in the kernel; o and lse are exactly what
  * fc_attn_fwd_partials followed by fc_lse_merge write. FC_FUSED computes
- * both sources in one online softmax. ws: device, >= fc_workspace_size. */
+ * both sources in one online softmax. On a view whose long key ranges are split
+ * (fc_view_export_split) either mode runs the chunks as workgroups of their
+ * own and merges them in a second launch, and the partial passes merge the
+ * same chunks in the same order, so o and lse remain what the partial passes
+ * and the merge write. ws: device, >= fc_workspace_size. */
 int fc_attn_fwd(fc_view view, const void* q, const void* k_loc, const void* v_loc,
                 const void* k_recv, const void* v_recv, float scale, int32_t mode,
                 void* o, float* o_f32, float* lse, void* ws, size_t ws_bytes, void* stream);
@@ -315,7 +348,10 @@ int fc_bwd_preprocess(fc_view view, const void* o, const float* o_f32, const voi
  * Key tiles seen by very many query tiles are split across workgroups that
  * write fp32 partials into ws, then summed in a fixed order, so dK/dV stay
  * reproducible. ws: device, >= the dkdv_bytes of fc_workspace_size; may be
- * NULL when that is 0 (no split key tile). */
+ * NULL when that is 0 (no split key tile). fc_attn_bwd_pass likewise splits
+ * the key ranges of query tiles that would outlast the rest of the launch and
+ * sums their partial dQ in a fixed order; fc_attn_bwd_dq, which takes no
+ * workspace, never does. */
 int fc_attn_bwd_dkdv(fc_view view, const void* q, const void* k_loc, const void* v_loc,
                      const void* k_recv, const void* v_recv, const float* lse, const float* delta,
                      const void* dout, float scale, float* dk_loc, float* dv_loc, float* dk_recv,

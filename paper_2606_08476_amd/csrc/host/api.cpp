@@ -53,8 +53,13 @@ struct FwdWs {
 // FC_TWO_PASS with received keys: the received partial's fp32 O (the
 // kernel merges it with the local partial in its epilogue), one slot of 32
 // rows x d per wave, four waves per workgroup of the launch
+// A split view, either mode: its chunks' partials.
 FwdWs fwd_ws(const View& v, int32_t mode) {
   FwdWs w{};
+  if (v.fwd_chunk) {
+    w.total = align_up(v.fwd_split_bytes());
+    return w;
+  }
   if (mode == FC_TWO_PASS && v.t_recv() > 0) {
     const size_t wgs = (v.fwd_fused.size() / 8) * size_t(v.hkv) *
                        size_t(v.hq / v.hkv / v.heads_per_tile);
@@ -63,11 +68,10 @@ FwdWs fwd_ws(const View& v, int32_t mode) {
   }
   return w;
 }
-size_t delta_ws(const View& v) { return align_up(size_t(v.t_q()) * v.hq * sizeof(float)); }
-size_t part_ws(const View& v) {
-  return 2 * size_t(v.n_bwd_slots) * v.hkv * v.bn_bwd * v.d * sizeof(float);
-}
-size_t bwd_ws(const View& v) { return delta_ws(v) + part_ws(v); }
+// the backward pass's workspace: partial dK/dV of split key tiles, then
+// partial dQ of split query tiles
+size_t pass_ws(const View& v) { return v.part_bytes() + v.dq_part_bytes(); }
+size_t bwd_ws(const View& v) { return v.delta_bytes() + pass_ws(v); }
 
 fck::FwdParams fwd_params(const View& v, const int32_t* items, int64_t n,
                           const void* q, const void* k_loc, const void* v_loc, const void* k_recv,
@@ -89,6 +93,20 @@ fck::FwdParams fwd_params(const View& v, const int32_t* items, int64_t n,
   return p;
 }
 
+// The chunks of a split view, in `slots` (null: no slots to be had).
+void set_chunks(fck::FwdParams& p, const View& v, void* slots) {
+  if (!v.fwd_chunk) return;
+  p.chunk = v.fwd_chunk;
+  p.units = v.dev_meta + v.off.fwd_units;
+  p.n_units = int32_t(v.fwd_units.size() / 8);
+  p.comb = v.dev_meta + v.off.fwd_comb;
+  p.n_comb = int32_t(v.fwd_comb.size() / 8);
+  p.slots = static_cast<float*>(slots);
+  if (slots)
+    p.slot_lse = reinterpret_cast<float*>(static_cast<char*>(slots) + v.fwd_slots_bytes());
+  for (int i = 0; i < 2; ++i) p.guard[i] = &v.slot_guard[i];
+}
+
 // Both partial passes of the two-pass forward in one launch over the fused
 // items: each workgroup runs its query tile's received range, writes that
 // partial (o_recv, lse_recv), then runs the local range (o_loc, lse_loc).
@@ -103,6 +121,7 @@ int launch_partials(const View& v, const void* q, const void* k_loc, const void*
   p.lse = lse_loc;
   p.o_f32_recv = o_recv;
   p.lse_recv = lse_recv;
+  set_chunks(p, v, v.dev_slots);
   return hip_status(fck::launch_fwd(p, v.d, v.heads_per_tile, false, s), "attn_fwd launch");
 }
 
@@ -178,13 +197,19 @@ int launch_reduce(const View& v, const fck::BwdParams& p, hipStream_t s) {
 int run_pass(const View& v, const void* q, const void* k_loc, const void* v_loc,
              const void* k_recv, const void* v_recv, const float* lse, const float* delta,
              const void* dout, float scale, int32_t deterministic, float* dq, float* dk_loc,
-             float* dv_loc, float* dk_recv, float* dv_recv, void* ws, size_t need,
+             float* dv_loc, float* dk_recv, float* dv_recv, void* ws, size_t ws_bytes,
              hipStream_t s) {
   fck::BwdParams p = bwd_params(v, q, k_loc, v_loc, k_recv, v_recv, lse, delta, dout, scale,
-                                dk_loc, dv_loc, dk_recv, dv_recv, ws, need);
+                                dk_loc, dv_loc, dk_recv, dv_recv, ws, v.part_bytes());
   if (deterministic) {
-    const fck::DqParams d = dq_params(v, q, k_loc, v_loc, k_recv, v_recv, lse, delta, dout,
-                                      scale, dq);
+    fck::DqParams d = dq_params(v, q, k_loc, v_loc, k_recv, v_recv, lse, delta, dout, scale, dq);
+    if (v.n_dq_slots && ws_bytes >= pass_ws(v)) {
+      d.items = v.dev_meta + v.off.dq_items;
+      d.n_items = int32_t(v.dq_items.size() / 8);
+      d.part = reinterpret_cast<float*>(static_cast<char*>(ws) + v.part_bytes());
+      d.comb = v.dev_meta + v.off.dq_comb;
+      d.n_comb = int32_t(v.dq_comb.size() / 8);
+    }
     if (int rc = hip_status(fck::launch_bwd_grid(p, d, v.d, v.heads_per_tile, s),
                             "attn_bwd launch"))
       return rc;
@@ -208,7 +233,7 @@ int fc_workspace_size(fc_view view, int32_t mode, size_t* fwd_bytes, size_t* bwd
   const View& v = *reinterpret_cast<View*>(view);
   if (fwd_bytes) *fwd_bytes = fwd_ws(v, mode).total;
   if (bwd_bytes) *bwd_bytes = bwd_ws(v);
-  if (dkdv_bytes) *dkdv_bytes = part_ws(v);
+  if (dkdv_bytes) *dkdv_bytes = pass_ws(v);
   return FC_OK;
 }
 
@@ -263,8 +288,16 @@ int fc_attn_fwd_partial(fc_view view, int32_t src, const void* q, const void* k_
                : fwd_params(*v, m + v->off.fwd_recv,
                             int64_t(v->fwd_recv.size() / 8), q, nullptr, nullptr, k_src, v_src,
                             scale);
-  p.o_f32 = o_part;
-  p.lse = lse_part;
+  if (p.n_items == 0) return FC_OK;
+  set_chunks(p, *v, v->dev_slots);
+  // (its units read both sources: the one not asked for is skipped)
+  if (src == 1 && p.chunk) {
+    p.o_f32_recv = o_part;
+    p.lse_recv = lse_part;
+  } else {
+    p.o_f32 = o_part;
+    p.lse = lse_part;
+  }
   return hip_status(fck::launch_fwd(p, v->d, v->heads_per_tile, false,
                                     reinterpret_cast<hipStream_t>(stream)),
                     "attn_fwd launch");
@@ -299,12 +332,23 @@ int fc_attn_fwd(fc_view view, const void* q, const void* k_loc, const void* v_lo
   if (!q || !k_loc || !v_loc || !o || !lse || (v->t_recv() && (!k_recv || !v_recv)))
     return fail(FC_ERR_INVALID_ARG, "null tensor pointer");
   const FwdWs w = fwd_ws(*v, mode);
-  if (ws_bytes < w.total || (w.total && !ws))
+  // (one pass needs no workspace: without one a split view takes it whole)
+  const bool one_pass = mode == FC_FUSED || v->t_recv() == 0;
+  const bool split = v->fwd_chunk && !(one_pass && (!ws || ws_bytes == 0));
+  if ((split || !one_pass) && (ws_bytes < w.total || (w.total && !ws)))
     return fail(FC_ERR_WORKSPACE, "forward workspace of " + std::to_string(ws_bytes) +
                                       " bytes, need " + std::to_string(w.total));
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const int32_t* m = v->dev_meta;
-  if (mode == FC_FUSED || v->t_recv() == 0) {
+  if (split) {
+    fck::FwdParams p = fwd_params(*v, nullptr, 0, q, k_loc, v_loc, k_recv, v_recv, scale);
+    set_chunks(p, *v, ws);
+    p.o_bf16 = static_cast<uint16_t*>(o);
+    p.o_f32 = o_f32;
+    p.lse = lse;
+    return hip_status(fck::launch_fwd(p, v->d, v->heads_per_tile, true, s), "attn_fwd launch");
+  }
+  if (one_pass) {
     // one pass: both sources (fused items), or the local source alone
     const bool fused = mode == FC_FUSED && v->t_recv() > 0;
     fck::FwdParams p =
@@ -377,7 +421,7 @@ int fc_attn_bwd_dkdv(fc_view view, const void* q, const void* k_loc, const void*
   if (!q || !k_loc || !v_loc || !lse || !delta || !dout || !dk_loc || !dv_loc ||
       (v->t_recv() && (!k_recv || !v_recv || !dk_recv || !dv_recv)))
     return fail(FC_ERR_INVALID_ARG, "null tensor pointer");
-  const size_t need = part_ws(*v);
+  const size_t need = v->part_bytes();
   if (need && (!ws || ws_bytes < need))
     return fail(FC_ERR_WORKSPACE, "dK/dV workspace of " + std::to_string(ws_bytes) +
                                       " bytes, need " + std::to_string(need));
@@ -421,7 +465,7 @@ int fc_attn_bwd_pass(fc_view view, const void* q, const void* k_loc, const void*
   if (!q || !k_loc || !v_loc || !lse || !delta || !dout || !dq || !dk_loc || !dv_loc ||
       (v->t_recv() && (!k_recv || !v_recv || !dk_recv || !dv_recv)))
     return fail(FC_ERR_INVALID_ARG, "null tensor pointer");
-  const size_t need = part_ws(*v);
+  const size_t need = v->part_bytes();
   if (need && (!ws || ws_bytes < need))
     return fail(FC_ERR_WORKSPACE, "dK/dV workspace of " + std::to_string(ws_bytes) +
                                       " bytes, need " + std::to_string(need));
@@ -430,7 +474,7 @@ int fc_attn_bwd_pass(fc_view view, const void* q, const void* k_loc, const void*
       hip_status(fck::launch_fill_zero(dq, int64_t(v->t_q()) * v->hq * v->d, s), "dq zero fill"))
     return FC_ERR_HIP;
   return run_pass(*v, q, k_loc, v_loc, k_recv, v_recv, lse, delta, dout, scale, deterministic,
-                  dq, dk_loc, dv_loc, dk_recv, dv_recv, ws, need, s);
+                  dq, dk_loc, dv_loc, dk_recv, dv_recv, ws, ws_bytes, s);
 }
 
 int fc_attn_bwd(fc_view view, const void* q, const void* k_loc, const void* v_loc,
@@ -462,10 +506,10 @@ int fc_attn_bwd(fc_view view, const void* q, const void* k_loc, const void* v_lo
                                                      deterministic ? nullptr : dq, s),
                           "bwd preprocess launch"))
     return rc;
-  const size_t dbytes = delta_ws(*v);
+  const size_t dbytes = v->delta_bytes();
   return run_pass(*v, q, k_loc, v_loc, k_recv, v_recv, lse, delta, dout, scale, deterministic,
                   dq, dk_loc, dv_loc, dk_recv, dv_recv, static_cast<char*>(ws) + dbytes,
-                  part_ws(*v), s);
+                  ws_bytes - dbytes, s);
 }
 
 }  // extern "C"

@@ -28,7 +28,15 @@ namespace fc {
 
 namespace {
 
+// workgroups resident at a time: 256 CUs, two per CU
+constexpr int64_t kSlotsResident = 512;
+
 int32_t ceil_div(int64_t a, int64_t b) { return int32_t((a + b - 1) / b); }
+
+// Microseconds a combine pass adds: a launch, a read latency per slot of a
+// tile, and `bytes` of slots written and read (measured at about 7 TB/s: many
+// are still in the caches).
+double combine_us(int32_t slots, double bytes) { return 4.0 + 0.7 * slots + 2 * bytes / 7e6; }
 
 // First tile start q0 + t*bm at or after `from`, or q1 if there is none.
 int32_t first_tile_at_or_after(int32_t q0, int32_t q1, int32_t bm, int64_t from) {
@@ -120,6 +128,8 @@ void View::build_tiles() {
   for (size_t i = 0; i < bc.size(); ++i) bc[i] = ceil_div(bwd[8 * i + 3] - bwd[8 * i + 2], bm_bwd);
   perm_bwd = lpt_order(bc);
   build_bwd_launch();
+  build_dq_split();
+  build_fwd_split();
 }
 
 // Split key tiles whose query range is much longer than a fair share of the
@@ -129,7 +139,6 @@ void View::build_tiles() {
 // writes fp32 partial dK/dV to its own slot and a reduce pass sums the parts
 // in slot order (deterministic).
 void View::build_bwd_launch() {
-  constexpr int64_t kSlotsResident = 512;
   const int64_t G = hq / hkv;
   const size_t n = bwd.size() / 8;
   int64_t total = 0;
@@ -190,6 +199,180 @@ void View::build_bwd_launch() {
   }
 }
 
+// Split the key range of query tiles whose dQ workgroup would be the critical
+// path of the backward grid: with few workgroups (few KV heads, short
+// sequences) or one document much longer than the rest, a tile that walks
+// thousands of keys alone ends long after everything else. Its key tiles are
+// cut into parts of at most `per` tiles, each part's sum goes to a slot of
+// its own and a combine pass adds the slots in key order (deterministic).
+// Whether to split, and into what, is decided by the grid's estimated time:
+// the larger of the resident slots' fair share and of the latest start plus
+// the longest item. The estimate's rates are measured: microseconds per dK/dV
+// iteration and per dQ key tile with two workgroups on the CU, per dQ key
+// tile alone on it, and per workgroup for its prologue and epilogue. Measured:
+// 8 query heads on one KV head, 64K tokens over 8 ranks (longest tile 295 of
+// the key tiles, 85 a fair share), backward 850 us whole, 636-645 us in parts
+// of 32 to 128 tiles, 721 in parts of 8; grids that fill the chip lose by it
+// (32/8 heads, 64K over 8 ranks: 1150 us whole, 1155 in parts of 128, 1205 of
+// 32), so nothing under a tenth of the estimate is split.
+void View::build_dq_split() {
+  dq_items.clear();
+  dq_comb.clear();
+  n_dq_slots = 0;
+  const bool wide = d == 128;
+  const double dk2 = wide ? 1.87 : 1.03, dq2 = wide ? 2.30 : 1.41, dq1 = wide ? 1.45 : 0.94;
+  const double wg = wide ? 9.0 : 4.0;
+  const int32_t G = hq / hkv, hpi = G % 4 == 0 ? 4 : G % 2 == 0 ? 2 : 1;
+  const size_t n = fwd_fused.size() / 8, nk = bwd_launch.size() / 8;
+  if (n == 0) return;
+  double dk_sum = 0, dk_max = 0;
+  for (size_t i = 0; i < nk; ++i) {
+    const int32_t* it = &bwd_launch[8 * i];
+    const double t = wg + dk2 * ceil_div(it[3] - it[2], 32 / hpi) * (G / hpi);
+    dk_sum += t * hkv;
+    dk_max = std::max(dk_max, t);
+  }
+  const double wgs = double(hkv) * head_chunks();  // workgroups per item
+  std::vector<int32_t> tiles(n);
+  int64_t total = 0;
+  int32_t longest = 0;
+  for (size_t i = 0; i < n; ++i) {
+    const int32_t* it = &fwd_fused[8 * i];
+    tiles[i] = ceil_div(it[3] - it[2], bn_fwd) + ceil_div(it[5] - it[4], bn_fwd);
+    total += tiles[i];
+    longest = std::max(longest, tiles[i]);
+  }
+  const double start = double(nk) * hkv >= kSlotsResident ? dk_sum / kSlotsResident : 0;
+  auto grid_us = [&](double parts, double most) {
+    const double fair = (dk_sum + wgs * (double(total) * dq2 + parts * wg)) / kSlotsResident;
+    return std::max({fair, dk_max, start + most * dq1 + wg});
+  };
+  const double whole = grid_us(double(n), longest);
+  const size_t base = delta_bytes() + part_bytes();
+  double best = 0.9 * whole;
+  int32_t per = 0;
+  for (int32_t log2c = 3; 1 << log2c < longest; ++log2c) {
+    const int32_t c = 1 << log2c;
+    if (grid_us(double(n), c) >= best) break;  // no split helps less than this one
+    int64_t parts = 0, slots = 0;
+    for (int32_t t : tiles) {
+      const int32_t k = (t + c - 1) >> log2c;
+      parts += k;
+      if (k > 1) slots += k;
+    }
+    const double bytes = double(slots) * slot_bytes();
+    // what fits the static scratch of fc_attn_bwd_noalloc unsplit still does
+    if (base <= FC_NOALLOC_SCRATCH_BYTES && base + bytes > FC_NOALLOC_SCRATCH_BYTES) continue;
+    const double us = grid_us(double(parts), c) + combine_us(ceil_div(longest, c), bytes);
+    if (us < best) {
+      best = us;
+      per = c;
+    }
+  }
+  if (!per) return;
+  std::vector<int32_t> items;
+  std::vector<int64_t> cost;
+  for (size_t i = 0; i < n; ++i) {
+    const int32_t* it = &fwd_fused[8 * i];
+    const int32_t n_r = ceil_div(it[3] - it[2], bn_fwd), k = ceil_div(tiles[i], per);
+    if (k > 1)
+      dq_comb.insert(dq_comb.end(), {it[0], it[1], n_dq_slots, k, 0, 0, 0, 0});
+    for (int32_t j = 0; j < k; ++j) {
+      // key tiles a .. b-1 of the item, received ones first
+      const int32_t a = int32_t(int64_t(tiles[i]) * j / k), b = int32_t(int64_t(tiles[i]) * (j + 1) / k);
+      const int32_t ra = std::min(a, n_r), rb = std::min(b, n_r);
+      const int32_t la = std::max(a, n_r) - n_r, lb = std::max(b, n_r) - n_r;
+      items.insert(items.end(), {it[0], it[1], std::min(it[2] + ra * bn_fwd, it[3]),
+                                 std::min(it[2] + rb * bn_fwd, it[3]),
+                                 std::min(it[4] + la * bn_fwd, it[5]),
+                                 std::min(it[4] + lb * bn_fwd, it[5]), it[6],
+                                 k > 1 ? n_dq_slots++ : -1});
+      cost.push_back(b - a);
+    }
+  }
+  for (int32_t i : lpt_order(cost))
+    dq_items.insert(dq_items.end(), &items[8 * size_t(i)], &items[8 * size_t(i)] + 8);
+}
+
+// Split the forward's key ranges where the longest query tile would be the
+// critical path of the launch, as build_dq_split does for dQ: each source's
+// keys are taken in chunks of `fwd_chunk` key tiles counted from the source's
+// first key of the query tile's document, which every query tile of the
+// document shares, so a row's chunks do not depend on the tile (or the entry
+// point) that computes it. Every query tile of a split view goes through
+// slots and the combine pass. The estimate's rates are measured: microseconds
+// per key tile with two workgroups on the CU and alone on it, and per
+// workgroup for its prologue and epilogue. Measured, the same 8/1-head view:
+// forward 331 us whole, 207-215 us in chunks of 32 to 128 tiles, 243 of 16; 8
+// query heads over one 4.8K-token sequence 71 -> 29 us. Grids that fill the chip
+// lose (64K whole documents: 243 us whole, 261 in chunks of 32), so the
+// estimate has to fall by 15%.
+void View::build_fwd_split() {
+  fwd_chunk = 0;
+  fwd_units.clear();
+  fwd_comb.clear();
+  const bool wide = d == 128;
+  const double f2 = wide ? 1.90 : 1.03, f1 = wide ? 1.09 : 0.86, wg = wide ? 9.0 : 4.0;
+  const size_t n = fwd_fused.size() / 8;
+  const double wgs = double(hkv) * head_chunks();
+  int64_t total = 0;
+  int32_t longest = 0;
+  std::vector<int32_t> tiles(2 * n);  // per item: received, local key tiles
+  for (size_t i = 0; i < n; ++i) {
+    const int32_t* it = &fwd_fused[8 * i];
+    tiles[2 * i] = ceil_div(it[3] - it[2], bn_fwd);
+    tiles[2 * i + 1] = ceil_div(it[5] - it[4], bn_fwd);
+    const int32_t t = tiles[2 * i] + tiles[2 * i + 1];
+    total += t;
+    longest = std::max(longest, t);
+  }
+  // a launch of more workgroups than fit ends, on average, some way into the
+  // longest of the items it starts last
+  auto launch_us = [&](double units, double most) {
+    const double fair = wgs * (double(total) * f2 + units * wg) / kSlotsResident;
+    const double tail = units * wgs > kSlotsResident ? 0.3 * most * f1 : 0;
+    return std::max(fair + tail, most * f1 + wg);
+  };
+  const double whole = launch_us(double(n), longest);
+  double best = 0.85 * whole;
+  int32_t chunk = 0;
+  for (int32_t log2c = 3; 1 << log2c < longest; ++log2c) {
+    const int32_t c = 1 << log2c;
+    if (launch_us(double(n), c) >= best) break;  // no chunk length helps less than this one
+    int64_t units = 0;
+    for (int32_t t : tiles) units += (t + c - 1) >> log2c;
+    const double us = launch_us(double(units), c) +
+                      combine_us(ceil_div(longest, c), double(units) * slot_bytes());
+    if (us < best) {
+      best = us;
+      chunk = c;
+    }
+  }
+  if (!chunk) return;
+  fwd_chunk = chunk;
+  const int32_t len = chunk * bn_fwd;
+  std::vector<int32_t> items;
+  std::vector<int64_t> cost;
+  fwd_comb.reserve(8 * n);
+  for (size_t i = 0; i < n; ++i) {
+    const int32_t* it = &fwd_fused[8 * i];
+    fwd_comb.insert(fwd_comb.end(), {it[0], it[1], int32_t(cost.size()), ceil_div(it[3] - it[2], len),
+                                     ceil_div(it[5] - it[4], len), 0, 0, 0});
+    for (int32_t a = it[2]; a < it[3]; a += len) {
+      const int32_t b = std::min(a + len, it[3]);
+      items.insert(items.end(), {it[0], it[1], a, b, 0, 0, 0, int32_t(cost.size())});
+      cost.push_back(ceil_div(b - a, bn_fwd));
+    }
+    for (int32_t a = it[4]; a < it[5]; a += len) {
+      const int32_t b = std::min(a + len, it[5]);
+      items.insert(items.end(), {it[0], it[1], 0, 0, a, b, it[6], int32_t(cost.size())});
+      cost.push_back(ceil_div(b - a, bn_fwd));
+    }
+  }
+  for (int32_t i : lpt_order(cost))
+    fwd_units.insert(fwd_units.end(), &items[8 * size_t(i)], &items[8 * size_t(i)] + 8);
+}
+
 // Every index the kernels will take from the tables, checked against the
 // extents they index (t_q, t_recv, the slot count) before anything is
 // uploaded: a table out of range is a library bug, reported as such rather
@@ -200,7 +383,7 @@ int View::check_tables() const {
     return fail(FC_ERR_INTERNAL, std::string("internal: ") + what + " entry " + std::to_string(i) +
                                      " out of range");
   };
-  for (const auto* list : {&fwd_local, &fwd_recv, &fwd_fused}) {
+  for (const auto* list : {&fwd_local, &fwd_recv, &fwd_fused, &dq_items, &fwd_units}) {
     for (size_t i = 0; i < list->size() / 8; ++i) {
       const int32_t* it = &(*list)[8 * i];
       if (!(0 <= it[0] && it[0] < it[1] && it[1] <= tq && it[1] - it[0] <= bm_fwd))
@@ -223,6 +406,24 @@ int View::check_tables() const {
     if (!((e[0] == 0 || e[0] == 1) && 0 <= e[1] && e[1] < e[2] && e[2] <= hi && 0 <= e[3] &&
           0 < e[4] && e[3] + e[4] <= n_bwd_slots))
       return bad("backward reduce entry", i);
+  }
+  for (size_t i = 0; i < dq_items.size() / 8; ++i)
+    if (!(-1 <= dq_items[8 * i + 7] && dq_items[8 * i + 7] < n_dq_slots)) return bad("dQ item", i);
+  for (size_t i = 0; i < dq_comb.size() / 8; ++i) {
+    const int32_t* e = &dq_comb[8 * i];
+    if (!(0 <= e[0] && e[0] < e[1] && e[1] <= tq && e[1] - e[0] <= bm_fwd && 0 <= e[2] &&
+          0 < e[3] && e[2] + e[3] <= n_dq_slots))
+      return bad("dQ combine entry", i);
+  }
+  const int32_t n_units = int32_t(fwd_units.size() / 8);
+  for (int32_t i = 0; i < n_units; ++i)
+    if (!(0 <= fwd_units[8 * size_t(i) + 7] && fwd_units[8 * size_t(i) + 7] < n_units))
+      return bad("forward chunk", size_t(i));
+  for (size_t i = 0; i < fwd_comb.size() / 8; ++i) {
+    const int32_t* e = &fwd_comb[8 * i];
+    if (!(0 <= e[0] && e[0] < e[1] && e[1] <= tq && e[1] - e[0] <= bm_fwd && 0 <= e[2] &&
+          0 <= e[3] && 0 <= e[4] && 0 < e[3] + e[4] && e[2] + e[3] + e[4] <= n_units))
+      return bad("forward combine entry", i);
   }
   if (bwd_qfirst.size() != bwd_launch.size() / 8 * size_t(bn_bwd / 32)) return bad("qfirst", 0);
   for (size_t i = 0; i < lim.size(); ++i)
@@ -255,6 +456,10 @@ void View::build_meta() {
   off.bwd_launch = put(bwd_launch);
   off.bwd_reduce = put(bwd_reduce);
   off.bwd_qfirst = put(bwd_qfirst);
+  off.dq_items = put(dq_items);
+  off.dq_comb = put(dq_comb);
+  off.fwd_units = put(fwd_units);
+  off.fwd_comb = put(fwd_comb);
   if (meta.empty()) meta.resize(64, 0);
 }
 
@@ -385,7 +590,7 @@ int fc_view_get_info(fc_view view, fc_view_info* out) {
   out->n_bwd = int64_t(v.bwd.size() / 8);
   out->pairs_loc = v.pairs_loc;
   out->pairs_recv = v.pairs_recv;
-  out->meta_bytes = int64_t(v.meta.size() * sizeof(int32_t));
+  out->meta_bytes = int64_t(v.table_bytes() + (v.fwd_chunk ? v.fwd_split_bytes() : 0));
   out->n_bwd_launch = int64_t(v.bwd_launch.size() / 8);
   out->n_bwd_reduce = int64_t(v.bwd_reduce.size() / 8);
   out->n_bwd_slots = v.n_bwd_slots;
@@ -433,11 +638,29 @@ int fc_view_export_launch(fc_view view, int32_t* fwd_local, int32_t* fwd_recv,
   return FC_OK;
 }
 
+int fc_view_export_split(fc_view view, int32_t counts[5], int32_t* dq_items, int32_t* dq_comb,
+                         int32_t* fwd_units, int32_t* fwd_comb) {
+  clear_error();
+  if (!view || !counts) return fail(FC_ERR_INVALID_ARG, "null argument");
+  const View& v = *reinterpret_cast<View*>(view);
+  counts[0] = v.fwd_chunk;
+  int k = 0;
+  auto cp = [&](int32_t* dst, int64_t off, const std::vector<int32_t>& t) {
+    counts[++k] = int32_t(t.size() / 8);
+    if (dst) std::copy(v.meta.begin() + off, v.meta.begin() + off + int64_t(t.size()), dst);
+  };
+  cp(dq_items, v.off.dq_items, v.dq_items);
+  cp(dq_comb, v.off.dq_comb, v.dq_comb);
+  cp(fwd_units, v.off.fwd_units, v.fwd_units);
+  cp(fwd_comb, v.off.fwd_comb, v.fwd_comb);
+  return FC_OK;
+}
+
 int fc_view_bind(fc_view view, void* dev_meta, size_t bytes, void* stream) {
   clear_error();
   if (!view || !dev_meta) return fail(FC_ERR_INVALID_ARG, "null argument");
   View& v = *reinterpret_cast<View*>(view);
-  const size_t need = v.meta.size() * sizeof(int32_t);
+  const size_t need = v.table_bytes();
   if (bytes < need)
     return fail(FC_ERR_WORKSPACE, "metadata buffer of " + std::to_string(bytes) +
                                       " bytes, need " + std::to_string(need));
@@ -447,6 +670,9 @@ int fc_view_bind(fc_view view, void* dev_meta, size_t bytes, void* stream) {
                                 reinterpret_cast<hipStream_t>(stream));
   if (e != hipSuccess) return fail(FC_ERR_HIP, std::string("hipMemcpyAsync: ") + hipGetErrorString(e));
   v.dev_meta = reinterpret_cast<const int32_t*>(dev_meta);
+  // (the tables end 256-byte aligned)
+  const bool slots = v.fwd_chunk && bytes >= need + v.fwd_split_bytes();
+  v.dev_slots = slots ? reinterpret_cast<float*>(static_cast<char*>(dev_meta) + need) : nullptr;
   return FC_OK;
 }
 

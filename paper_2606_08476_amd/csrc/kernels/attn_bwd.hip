@@ -55,7 +55,8 @@ static hipError_t launch_grid_d(const BwdParams& bp, const DqParams& dp, int hpw
   else if (hpi == 1 && hpw == 1) FC_GRID(1, 1);
   else return hipErrorInvalidValue;
 #undef FC_GRID
-  return hipGetLastError();
+  if (const hipError_t e = hipGetLastError(); e != hipSuccess || !dp.n_comb) return e;
+  return launch_dq_combine_d<D>(dp, hpw, s);
 }
 
 hipError_t launch_bwd_grid(const BwdParams& bp, const DqParams& dp, int d, int heads_per_tile,

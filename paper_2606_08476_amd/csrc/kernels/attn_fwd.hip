@@ -31,6 +31,19 @@
 // epilogue: the received partial's O is written to a workspace at the
 // switch and read back at the end, its LSE kept in a register, and the
 // final O and LSE are written as the merge kernel would write them.
+//
+// Split views. With few workgroups, or one much longer than the rest, the
+// launch lasts as long as its longest key range. The host then gives the
+// view a chunk length: each source's keys are taken in chunks of that many
+// key tiles, each chunk an online softmax of its own, and a source's partial
+// is the chunks' partials merged in key order. The chunks are work items of
+// their own (OUT = unit: partial O to a slot, in register order, with its
+// LSE), and fwd_combine_kernel merges them, in slots of the caller's workspace
+// or, for the partial passes, of the view's bound buffer. Where neither is to
+// be had (a partial pass under stream capture, or a view bound without its
+// slots) one workgroup runs its chunks one after the other and merges as it
+// goes (OUT = chunks), keeping the merged chunks in its own rows of the
+// output. All of them give the same bits.
 #include "common.hpp"
 #include "launch.hpp"
 
@@ -38,11 +51,19 @@
 
 namespace fck {
 
-enum { kOutPartial = 0, kOutFinal = 1, kOutPaired = 2, kOutMerged = 3 };
+enum {
+  kOutPartial = 0,
+  kOutFinal = 1,
+  kOutPaired = 2,
+  kOutMerged = 3,
+  kOutUnit = 4,
+  kOutChunks = 5
+};
 
 template <int D, int HPW, int OUT>
 __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
-  constexpr bool FINAL = OUT == kOutFinal, MERGED = OUT == kOutMerged;
+  constexpr bool FINAL = OUT == kOutFinal, MERGED = OUT == kOutMerged, UNIT = OUT == kOutUnit;
+  constexpr bool CHUNKS = OUT == kOutChunks;
   constexpr bool PAIRED = OUT == kOutPaired || MERGED;
   constexpr int BN = 64;        // keys per tile
   constexpr int RPW = 32 / HPW;  // query rows per wave and head
@@ -67,9 +88,11 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   const int kvh = b % p.hkv;
   const int rest = b / p.hkv;
   const int hc = rest % p.head_chunks;
-  const int32_t* it = p.items + 8 * (rest / p.head_chunks);
+  const int32_t* it = (UNIT ? p.units : p.items) + 8 * (rest / p.head_chunks);
   const int q0 = it[0], q1 = it[1], r0 = it[2], r1 = it[3], l0 = it[4], l1 = it[5];
   const int ldiag = it[6];
+  // a chunk of the source that this partial pass does not compute
+  if (UNIT && !p.o_bf16 && !(r1 > r0 ? p.o_f32_recv : p.o_f32)) return;
 
   // lane -> (query row, head): a wave takes RPW consecutive rows of each of
   // the HPW heads, so a short query range leaves whole waves without rows
@@ -184,6 +207,90 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
     lsum = 0.f;
   };
 
+  // CHUNKS: the end of a chunk of `recv` keys. Its partial (with the source's
+  // chunks before it merged in, unless it is the first) becomes oacc and
+  // lse_acc; then it is kept for the next chunk, or (`done`, the source's
+  // last chunk, the local keys still to come) stored, and the next chunk
+  // starts from empty. At the end of the workgroup's keys (`end`) it stays in
+  // oacc for the epilogue.
+  float lse_acc = -INFINITY;
+  auto finish_chunk = [&](bool recv, bool first, bool done, bool end) __attribute__((always_inline)) {
+    const float tot = sum_halves(lsum);
+    const float inv = tot > 0.f ? 1.f / tot : 0.f;
+    const float lse = tot > 0.f ? (m + __log2f(tot)) * kLn2 : -INFINITY;
+    float* const out = recv ? p.o_f32_recv : p.o_f32;
+    float* const out_lse = recv ? p.lse_recv : p.lse;
+    // the merged chunks in the output: this wave's nv rows of every head, taken
+    // as nv * HPW * D floats in register order (instruction k holds 4 floats of
+    // each lane with a row, side by side)
+    // (lane-derived offsets from an opaque copy of the lane index: not held
+    // across the key loop)
+    const int ln = int(opaque(uint32_t(lane))), pr = ln & 31;
+    const int nv = min(RPW, q1 - (q0 + wave * RPW));
+    const int ci = 2 * ((pr / RPW) * nv + pr % RPW) + (ln >> 5);
+    float* const rows = out + (size_t(q0 + wave * RPW) * p.hq + kvh * p.group + hc * HPW) * D;
+    auto raw = [&](int k) {
+      const int L = k * (nv * HPW * 8) + 4 * ci;
+      return rows + (L / (HPW * D)) * p.hq * D + L % (HPW * D);
+    };
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) oacc[db][i] *= inv;
+    if (first) {
+      lse_acc = lse;
+    } else {
+      const Merge2 w = merge2(lse_acc, lse);
+      lse_acc = w.lse;
+      if (qvalid) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db) {
+          f32x4 y[4];
+#pragma unroll
+          for (int g = 0; g < 4; ++g) y[g] = *reinterpret_cast<const f32x4*>(raw(4 * db + g));
+#pragma unroll
+          for (int i = 0; i < 16; ++i)
+            oacc[db][i] = merge2_value(w, y[i / 4][i % 4], oacc[db][i]);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      // every row of the kept chunks has been read before any is written over
+      wait_async();
+    }
+    if (end) return;
+    if (!done) {
+      if (qvalid) {
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+          for (int g = 0; g < 4; ++g) {
+            f32x4 v;
+#pragma unroll
+            for (int jj = 0; jj < 4; ++jj) v[jj] = oacc[db][4 * g + jj];
+            *reinterpret_cast<f32x4*>(raw(4 * db + g)) = v;
+          }
+      }
+    } else if (qvalid) {
+      const size_t ob = ((size_t)qrow * p.hq + h) * D;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          f32x4 v;
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) v[jj] = oacc[db][4 * g + jj];
+          *reinterpret_cast<f32x4*>(out + ob + 32 * db + 8 * g + 4 * half) = v;
+        }
+      if (half == 0) out_lse[(size_t)h * p.t_q + qrow] = lse_acc;
+    }
+#pragma unroll
+    for (int db = 0; db < DB; ++db) oacc[db] = zero16();
+    m = -INFINITY;
+    lsum = 0.f;
+  };
+  // CHUNKS: first key tile after the current chunk
+  int chunk_end = CHUNKS ? (n_r > 0 ? min(p.chunk, n_r) : min(p.chunk, n_t)) : 0;
+
   // S^T = K Q^T for the K tile at byte offset ko (prologue only; the loop
   // interleaves the same products with the softmax), two independent
   // accumulator chains (32 keys each)
@@ -256,6 +363,12 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
     if (j + 1 < n_t) fetch(j + 1, (3 - PAR) * TILE, true);   // V of tile j+1
     if (j + 2 < n_t) fetch(j + 2, PAR * TILE, false);        // K of tile j+2
     if (PAIRED && j == n_r) switch_source();
+    if (CHUNKS && j == chunk_end) {
+      const bool recv = j <= n_r;
+      const int c0 = recv ? 0 : n_r;  // the source's first key tile
+      if (active) finish_chunk(recv, j - c0 <= p.chunk, j == n_r, false);
+      chunk_end = min(j + p.chunk, j < n_r ? n_r : n_t);
+    }
     if (active) {
       // a row's output is rescaled only when its maximum grows by more than
       // the headroom; rows that do not grow keep their maximum and scale by 1
@@ -334,16 +447,55 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
     wait_async();
     __syncthreads();
   };
+  // no received key: the received partial (where one is asked for beside the
+  // local one) is empty
+  if (CHUNKS && n_r == 0 && p.o_f32 && p.o_f32_recv && active)
+    finish_chunk(true, true, true, false);
   for (int j = 0; j < n_t; j += 2) {
     step(j, std::integral_constant<int, 0>(), sa, mxa, sb, mxb);
     if (j + 1 < n_t) step(j + 1, std::integral_constant<int, 1>(), sb, mxb, sa, mxa);
   }
 
   if (PAIRED && n_r == n_t) switch_source();  // no local tile (never empty in practice)
+  if constexpr (CHUNKS) {
+    // the last source's partial: in oacc, normalised, after its last chunk
+    const bool recv = !p.o_f32;
+    if (active) finish_chunk(recv, n_t - (recv ? 0 : n_r) <= p.chunk, true, true);
+    store_rows<D, RPW>(
+        smem + size_t(wave) * (32 * D * 4), active,
+        [&](int db, int g) {
+          f32x4 v;
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) v[jj] = oacc[db][4 * g + jj];
+          return v;
+        },
+        q0 + wave * RPW, q1, p.hq, kvh * p.group + hc * HPW, recv ? p.o_f32_recv : p.o_f32,
+        nullptr);
+    if (qvalid && half == 0)
+      (recv ? p.lse_recv : p.lse)[(size_t)h * p.t_q + qrow] = lse_acc;
+    return;
+  }
   // the local (or only) partial, normalised, and its LSE
   const float tot = sum_halves(lsum);
   const float inv = tot > 0.f ? 1.f / tot : 0.f;
   const float lse_own = tot > 0.f ? (m + __log2f(tot)) * kLn2 : -INFINITY;
+  if constexpr (UNIT) {
+    const size_t sl = (size_t(it[7]) * p.head_chunks + hc) * p.hkv + kvh;
+    if (active) {
+      float* const o = p.slots + (sl * 4 + wave) * (32 * D) + 4 * lane;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          f32x4 v;
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) v[jj] = oacc[db][4 * g + jj] * inv;
+          *reinterpret_cast<f32x4*>(o + 256 * (4 * db + g)) = v;
+        }
+      if (half == 0) p.slot_lse[sl * 128 + 32 * wave + l31] = lse_own;
+    }
+    return;
+  }
   // rows go out through the LDS tile buffers, free once the loop's last
   // barrier has passed: wave w's region is bytes 32*D*4*w ..
   char* const region = smem + size_t(wave) * (32 * D * 4);
@@ -387,10 +539,128 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
   }
 }
 
+// The chunks of a split view's query tiles, merged: a source's chunks in key
+// order, then (FINAL) the local with the received partial, as the merge kernel
+// would, or each source's partial by itself. One wave per workgroup, for one wave's 32 rows of an entry (q0 q1 first-slot
+// received-chunks local-chunks 0 0 0). Bound by the latency of its reads (a
+// chunk's slot is read while the one before is merged).
+template <int D, int HPW, bool FINAL>
+__global__ __launch_bounds__(64) void fwd_combine_kernel(FwdParams p) {
+  constexpr int RPW = 32 / HPW, NK = D / 8;  // NK: 16-byte pieces per lane
+  __shared__ __attribute__((aligned(16))) char smem[32 * D * 4];
+  const int lane = threadIdx.x, l31 = lane & 31, half = lane >> 5;
+  const int wave = blockIdx.x & 3, b = blockIdx.x >> 2;
+  const int kvh = b % p.hkv, rest = b / p.hkv, hc = rest % p.head_chunks;
+  const int32_t* e = p.comb + 8 * (rest / p.head_chunks);
+  const int q0 = e[0], q1 = e[1], first = e[2], n_r = e[3], n_l = e[4];
+  if (q0 + wave * RPW >= q1) return;
+  auto slot = [&](int c) { return (size_t(first + c) * p.head_chunks + hc) * p.hkv + kvh; };
+  auto read = [&](f32x4 (&x)[NK], float& l, int c) {
+    const size_t sl = slot(c);
+    const float* const o = p.slots + (sl * 4 + wave) * (32 * D) + 4 * lane;
+#pragma unroll
+    for (int k = 0; k < NK; ++k) x[k] = *reinterpret_cast<const f32x4*>(o + 256 * k);
+    l = p.slot_lse[sl * 128 + 32 * wave + l31];
+  };
+  auto merge = [&](f32x4 (&a)[NK], float& la, const f32x4 (&x)[NK], float lx) {
+    const Merge2 w = merge2(la, lx);
+    la = w.lse;
+#pragma unroll
+    for (int k = 0; k < NK; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) a[k][j] = merge2_value(w, a[k][j], x[k][j]);
+  };
+  // chunks c0 .. c1-1 of one source, each read while the one before is merged
+  auto source = [&](f32x4 (&a)[NK], float& la, int c0, int c1) __attribute__((always_inline)) {
+    f32x4 x[NK], y[NK];
+    float lx = 0.f, ly = 0.f;
+    read(a, la, c0);
+    if (c0 + 1 < c1) read(x, lx, c0 + 1);
+    for (int c = c0 + 1; c < c1; c += 2) {
+      if (c + 1 < c1) read(y, ly, c + 1);
+      merge(a, la, x, lx);
+      if (c + 2 < c1) read(x, lx, c + 2);
+      if (c + 1 < c1) merge(a, la, y, ly);
+    }
+  };
+  const int h0 = kvh * p.group + hc * HPW;
+  auto put = [&](const f32x4 (&a)[NK], float la, float* of, u16* ob, float* lse) {
+    store_rows<D, RPW>(
+        smem, true, [&](int db, int g) { return a[4 * db + g]; }, q0 + wave * RPW, q1, p.hq, h0, of,
+        ob);
+    const int qrow = q0 + wave * RPW + l31 % RPW;
+    if (half == 0 && qrow < q1) lse[(size_t)(h0 + l31 / RPW) * p.t_q + qrow] = la;
+  };
+  f32x4 a[NK], r[NK];
+  float la = -INFINITY, lr = -INFINITY;
+  // (a source with no chunk: an empty partial)
+#pragma unroll
+  for (int k = 0; k < NK; ++k) a[k] = r[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool local = FINAL || p.o_f32, recv = FINAL || p.o_f32_recv;
+  if (local && n_l > 0) source(a, la, n_r, n_r + n_l);
+  if (recv && n_r > 0) source(r, lr, 0, n_r);
+  if constexpr (FINAL) {
+    merge(a, la, r, lr);
+    put(a, la, p.o_f32, p.o_bf16, p.lse);
+  } else {
+    if (local) put(a, la, p.o_f32, nullptr, p.lse);
+    __syncthreads();
+    if (recv) put(r, lr, p.o_f32_recv, nullptr, p.lse_recv);
+  }
+}
+
+// The chunks as workgroups, then their merge.
+template <int D, int HPW>
+static hipError_t launch_units_t(const FwdParams& p, hipStream_t s) {
+  const dim3 grid(unsigned(p.n_units) * p.hkv * p.head_chunks), block(256);
+  hipLaunchKernelGGL((attn_fwd_kernel<D, HPW, kOutUnit>), grid, block, 0, s, p);
+  if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  const dim3 cgrid(unsigned(p.n_comb) * p.hkv * p.head_chunks * 4);
+  if (p.o_bf16)
+    hipLaunchKernelGGL((fwd_combine_kernel<D, HPW, true>), cgrid, dim3(64), 0, s, p);
+  else
+    hipLaunchKernelGGL((fwd_combine_kernel<D, HPW, false>), cgrid, dim3(64), 0, s, p);
+  return hipGetLastError();
+}
+
+// A partial pass of a split view in the view's own slots: after the last use
+// of the slots (of each source it computes), before the next.
+template <int D, int HPW>
+static hipError_t launch_partial_units_t(const FwdParams& p, hipStream_t s) {
+  std::unique_lock<std::mutex> lock[2];
+  SlotGuard* used[2] = {p.o_f32 ? p.guard[0] : nullptr, p.o_f32_recv ? p.guard[1] : nullptr};
+  for (int i = 0; i < 2; ++i) {
+    SlotGuard* const g = used[i];
+    if (!g) continue;
+    lock[i] = std::unique_lock<std::mutex>(g->mu);
+    if (g->event) {
+      if (const hipError_t e = hipStreamWaitEvent(s, static_cast<hipEvent_t>(g->event), 0);
+          e != hipSuccess)
+        return e;
+    } else {
+      hipEvent_t ev;
+      if (const hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming); e != hipSuccess)
+        return e;
+      g->destroy = [](void* x) { (void)hipEventDestroy(static_cast<hipEvent_t>(x)); };
+      g->event = ev;
+    }
+  }
+  if (const hipError_t e = launch_units_t<D, HPW>(p, s); e != hipSuccess) return e;
+  for (SlotGuard* g : used)
+    if (g)
+      if (const hipError_t e = hipEventRecord(static_cast<hipEvent_t>(g->event), s); e != hipSuccess)
+        return e;
+  return hipSuccess;
+}
+
 template <int D, int HPW>
 static hipError_t launch_fwd_t(const FwdParams& p, int out, hipStream_t s) {
+  if (out == kOutUnit)
+    return p.o_bf16 ? launch_units_t<D, HPW>(p, s) : launch_partial_units_t<D, HPW>(p, s);
   const dim3 grid(unsigned(p.n_items) * p.hkv * p.head_chunks), block(256);
-  if (out == kOutFinal)
+  if (out == kOutChunks)
+    hipLaunchKernelGGL((attn_fwd_kernel<D, HPW, kOutChunks>), grid, block, 0, s, p);
+  else if (out == kOutFinal)
     hipLaunchKernelGGL((attn_fwd_kernel<D, HPW, kOutFinal>), grid, block, 0, s, p);
   else if (out == kOutPaired)
     hipLaunchKernelGGL((attn_fwd_kernel<D, HPW, kOutPaired>), grid, block, 0, s, p);
@@ -413,9 +683,22 @@ static hipError_t launch_fwd_d(const FwdParams& p, int hpw, int out, hipStream_t
 
 hipError_t launch_fwd(const FwdParams& p, int d, int heads_per_tile, bool final_out,
                       hipStream_t s) {
-  if (p.n_items == 0) return hipSuccess;
-  const int out = p.o_f32_recv ? (final_out ? kOutMerged : kOutPaired)
-                  : final_out ? kOutFinal : kOutPartial;
+  if (p.n_items == 0 && p.n_units == 0) return hipSuccess;
+  // (a captured partial pass may be replayed on any stream, where no event
+  // orders its use of the view's slots)
+  bool slots = p.slots != nullptr;
+  if (slots && !p.o_bf16) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+      (void)hipGetLastError();
+      slots = false;
+    }
+  }
+  const int out = slots           ? kOutUnit
+                  : p.chunk       ? kOutChunks
+                  : p.o_f32_recv  ? (final_out ? kOutMerged : kOutPaired)
+                  : final_out     ? kOutFinal
+                                  : kOutPartial;
   if (d == 64) return launch_fwd_d<64>(p, heads_per_tile, out, s);
   if (d == 128) return launch_fwd_d<128>(p, heads_per_tile, out, s);
   return hipErrorInvalidValue;

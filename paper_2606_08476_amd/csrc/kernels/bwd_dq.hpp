@@ -218,6 +218,26 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
     if (j + 1 < n_t) step(j + 1, std::integral_constant<int, 1>());
   }
 
+  // a part of a split key range: the unscaled sums go to the part's slot, in
+  // register order (1 KiB per store instruction), and are added up by
+  // dq_combine_kernel
+  if (p.part && it[7] >= 0) {
+    if (active) {
+      const size_t slot = (size_t(it[7]) * p.head_chunks + hc) * p.hkv + kvh;
+      float* const sl = p.part + (slot * 4 + wave) * (32 * D) + 4 * lane;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          f32x4 v;
+#pragma unroll
+          for (int jj = 0; jj < 4; ++jj) v[jj] = dq[db][4 * g + jj];
+          *reinterpret_cast<f32x4*>(sl + 256 * (4 * db + g)) = v;
+        }
+    }
+    return;
+  }
+
   // dQ rows out through this wave's share of the (now free) K/V buffers,
   // 1 KiB per store instruction
   store_rows<D, RPW>(
@@ -229,6 +249,70 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
         return v;
       },
       q0 + wave * RPW, q1, p.hq, kvh * p.group + hc * HPW, p.dq, nullptr);
+}
+
+// dQ of a query tile whose key range was split: the parts' slots added in
+// slot order (key order), scaled and stored. One wave per workgroup, for one
+// wave's 32 rows, so that few tiles still spread over the chip; two slots are
+// in flight at once. Bound by the latency of its reads.
+template <int D, int HPW>
+__global__ __launch_bounds__(64) void dq_combine_kernel(DqParams p) {
+  constexpr int RPW = 32 / HPW, DB = D / 32;
+  __shared__ __attribute__((aligned(16))) char smem[32 * D * 4];
+  const int lane = threadIdx.x;
+  const int wave = blockIdx.x & 3, b = blockIdx.x >> 2;
+  const int kvh = b % p.hkv, rest = b / p.hkv, hc = rest % p.head_chunks;
+  const int32_t* e = p.comb + 8 * (rest / p.head_chunks);
+  const int q0 = e[0], q1 = e[1], first = e[2], n = e[3];
+  if (q0 + wave * RPW >= q1) return;
+  auto at = [&](int s) {
+    const size_t slot = (size_t(first + s) * p.head_chunks + hc) * p.hkv + kvh;
+    return p.part + (slot * 4 + wave) * (32 * D) + 4 * lane;
+  };
+  f32x4 acc[4 * DB];
+#pragma unroll
+  for (int k = 0; k < 4 * DB; ++k) acc[k] = *reinterpret_cast<const f32x4*>(at(0) + 256 * k);
+  int s = 1;
+  for (; s + 1 < n; s += 2) {
+    f32x4 x[4 * DB], y[4 * DB];
+#pragma unroll
+    for (int k = 0; k < 4 * DB; ++k) x[k] = *reinterpret_cast<const f32x4*>(at(s) + 256 * k);
+#pragma unroll
+    for (int k = 0; k < 4 * DB; ++k) y[k] = *reinterpret_cast<const f32x4*>(at(s + 1) + 256 * k);
+#pragma unroll
+    for (int k = 0; k < 4 * DB; ++k)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[k][j] = (acc[k][j] + x[k][j]) + y[k][j];
+  }
+  if (s < n) {
+#pragma unroll
+    for (int k = 0; k < 4 * DB; ++k) {
+      const f32x4 x = *reinterpret_cast<const f32x4*>(at(s) + 256 * k);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) acc[k][j] += x[j];
+    }
+  }
+  store_rows<D, RPW>(
+      smem, true,
+      [&](int db, int g) {
+        f32x4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) v[j] = p.scale * acc[4 * db + g][j];
+        return v;
+      },
+      q0 + wave * RPW, q1, p.hq, kvh * p.group + hc * HPW, p.dq, nullptr);
+}
+
+template <int D>
+static hipError_t launch_dq_combine_d(const DqParams& p, int hpw, hipStream_t s) {
+  const dim3 grid(unsigned(p.n_comb) * p.hkv * p.head_chunks * 4), block(64);
+  switch (hpw) {
+    case 1: hipLaunchKernelGGL((dq_combine_kernel<D, 1>), grid, block, 0, s, p); break;
+    case 2: hipLaunchKernelGGL((dq_combine_kernel<D, 2>), grid, block, 0, s, p); break;
+    case 4: hipLaunchKernelGGL((dq_combine_kernel<D, 4>), grid, block, 0, s, p); break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace fck

@@ -5,7 +5,22 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
+
 namespace fck {
+
+// Orders the uses of a view's own partial slots: every use waits, on its
+// stream, for the event the last use recorded there, so uses on several
+// streams or threads follow one another instead of racing. The event is made
+// by the first launch (which also says how to destroy it).
+struct SlotGuard {
+  std::mutex mu;
+  void* event = nullptr;
+  void (*destroy)(void*) = nullptr;
+  ~SlotGuard() {
+    if (event) destroy(event);
+  }
+};
 
 struct FwdParams {
   const uint16_t* q;        // [t_q, hq, d] bf16
@@ -29,6 +44,23 @@ struct FwdParams {
   // O/LSE written as for the one-pass final output
   float* o_f32_recv;
   float* lse_recv;
+  // split views (non-zero chunk: key tiles per chunk). With slots: `units` are
+  // the chunks, last field the slot; slots of 128 x d floats and 128 LSEs per
+  // KV head and head chunk, merged per entry of `comb` (q0 q1 first-slot
+  // received-chunks local-chunks 0 0 0) into the final output, or for the
+  // partial passes into each source's partial: the local one to o_f32/lse, the
+  // received one to o_f32_recv/lse_recv, either null if not asked for; these
+  // use the view's own slots, guard[0] for the local chunks' and guard[1] for
+  // the received ones'. Without slots (partial passes): `items`, a workgroup
+  // per query tile merging its chunks itself.
+  int32_t chunk;
+  const int32_t* units;
+  int32_t n_units;
+  float* slots;
+  float* slot_lse;
+  const int32_t* comb;
+  int32_t n_comb;
+  SlotGuard* guard[2];
 };
 
 struct BwdParams {
@@ -71,6 +103,13 @@ struct DqParams {
   float scale;
   float* dq;                // [t_q, hq, d] fp32, written
   int32_t t_q;
+  // split key ranges (non-null part): the items are parts, the last field is
+  // the partial slot (-1: the whole range, written to dq directly); slots of
+  // 128 x d floats per KV head and head chunk, summed per entry of `comb`
+  // (q0 q1 first-slot slot-count 0 0 0 0) in slot order
+  float* part;
+  const int32_t* comb;
+  int32_t n_comb;
 };
 
 hipError_t launch_fwd(const FwdParams& p, int d, int heads_per_tile, bool final_out,

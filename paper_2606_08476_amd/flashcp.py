@@ -28,7 +28,7 @@ ERRORS = {
 EXPORTS = [
     "fc_plan_per_doc", "fc_plan_per_seq", "fc_plan_whole_lpt", "fc_plan_hybrid", "fc_plan_validate",
     "fc_plan_stats", "fc_view_create", "fc_view_get_info", "fc_view_export", "fc_view_bind",
-    "fc_view_destroy", "fc_view_export_launch", "fc_workspace_size", "fc_kv_gather", "fc_attn_fwd",
+    "fc_view_destroy", "fc_view_export_launch", "fc_view_export_split", "fc_workspace_size", "fc_kv_gather", "fc_attn_fwd",
     "fc_attn_fwd_partial", "fc_attn_fwd_partials", "fc_lse_merge", "fc_attn_bwd", "fc_bwd_preprocess",
     "fc_attn_bwd_pass", "fc_attn_bwd_dkdv", "fc_attn_bwd_dq", "fc_attn_bwd_noalloc", "fc_last_error",
 ]
@@ -96,6 +96,7 @@ def lib():
             "fc_view_export": [P] + [I32P] * 11,
             "fc_view_bind": [P, P, C.c_size_t, P],
             "fc_view_export_launch": [P] + [I32P] * 6,
+            "fc_view_export_split": [P] + [I32P] * 5,
             "fc_workspace_size": [P, C.c_int32, C.POINTER(C.c_size_t), C.POINTER(C.c_size_t),
                                   C.POINTER(C.c_size_t)],
             "fc_kv_gather": [P, P, P, C.c_int64, P, P, P, P, P],
@@ -260,6 +261,18 @@ class View:
         out = {k: arrs[k][:sizes[k]].reshape(-1, 8) for k in sizes if k != "bwd_qfirst"}
         out["bwd_qfirst"] = arrs["bwd_qfirst"][:sizes["bwd_qfirst"]].reshape(-1, nw)
         return out
+
+    def export_split(self) -> dict:
+        """The split key ranges (fc_view_export_split): ``fwd_chunk`` and the
+        four tables."""
+        n = np.zeros(5, dtype=np.int32)
+        p = n.ctypes.data_as(I32P)
+        _check(lib().fc_view_export_split(self.handle, p, None, None, None, None))
+        out = {k: np.zeros((int(m), 8), dtype=np.int32)
+               for k, m in zip(("dq_items", "dq_comb", "fwd_units", "fwd_comb"), n[1:])}
+        _check(lib().fc_view_export_split(self.handle, p, *[a.ctypes.data_as(I32P)
+                                                            for a in out.values()]))
+        return dict(out, fwd_chunk=int(n[0]))
 
     def bind(self, device="cuda", buf=None):
         """Upload the view's tables on the current stream into ``buf`` (a

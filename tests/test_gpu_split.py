@@ -1,0 +1,151 @@
+"""Views whose long key ranges are split over workgroups (few KV heads, one
+document much longer than the rest): every entry point against the fp64 oracle
+and against the others.
+
+The cases have key ranges that are whole multiples of the chunk length, one key
+more, shorter than one chunk and empty, one-token documents, both head dims and
+1, 4 and 8 query heads per KV head; the partial passes run over the view's own
+slots and, bound without them or captured into a graph, in one workgroup per
+query tile. Tolerances are those of the unsplit paths (test_gpu_parity);
+where the same sums are taken in another order in fp32, 2e-5 of the largest
+value (a few hundred roundings of 2^-24).
+"""
+import pytest
+import torch
+
+import _cases
+from oracle import attention as A
+from paper_2606_08476_amd import flashcp as F
+from test_gpu_parity import G_TOL, LSE_TOL, O_TOL, Run, _lse_ok, _maxabs, dev, say  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+ORDER_TOL = 2e-5
+
+CASES = {
+    # local keys only, whole multiples of the chunk length and one key more
+    "local_g4": dict(workload="llama8b", lens=[4096, 1, 2049, 512], cp=1, rank=0, hq=4, hkv=1,
+                     plan="whole_lpt"),
+    # received and local keys
+    "long_g8": dict(workload="longdoc", lens=[20001, 1, 70, 600], cp=8, rank=7, hq=8, hkv=1,
+                    plan="per_doc"),
+    "long_g4": dict(workload="longdoc", lens=[24000, 1, 70, 600], cp=16, rank=14, hq=4, hkv=1,
+                    plan="per_doc"),
+    # one long document among many of a few tokens
+    "skewed_g8": dict(workload="llama8b", lens=[24000] + [40] * 100, cp=8, rank=7, hq=8, hkv=1,
+                      plan="per_doc"),
+    "aligned_d64_g8": dict(workload="tiny", lens=[16384, 1024, 64], cp=8, rank=7, hq=16, hkv=2,
+                           plan="per_doc"),
+    "long_d64_g1": dict(workload="tiny", lens=[7001, 1, 1, 300], cp=2, rank=1, hq=4, hkv=4,
+                        plan="per_doc"),
+}
+
+
+@pytest.mark.parametrize("key", list(CASES))
+def test_split_views(key, dev):  # noqa: F811
+    kw = dict(CASES[key])
+    case = _cases.make_case(key, kw.pop("workload"), **kw)
+    r = Run(case, dev)
+    i, s = r.v.info, r.v.export_split()
+    tq, tr, hq, hkv, d = i["t_q"], i["t_recv"], i["hq"], i["hkv"], i["d"]
+    wgs = i["n_fwd_fused"] * hkv * (hq // hkv // (128 // i["bm_fwd"]))
+    say(f"[gpu] {key}: t_q {tq} t_recv {tr} workgroups {wgs} chunk {s['fwd_chunk']} "
+        f"dQ slots {int(s['dq_comb'][:, 3].sum())}")
+    assert s["fwd_chunk"] and (len(s["dq_comb"]) or key == "local_g4")
+    # forward and backward against the oracle
+    c, o, x = case, case.oview, r.x
+    O, L = r.oracle_fwd()
+    assert max(_maxabs(r.o, O), _maxabs(r.o32, O)) <= O_TOL and _lse_ok(r.lse, L) <= LSE_TOL
+    dq, dk, dv = r.oracle_bwd()
+    e = dict(dq=_maxabs(r.dq, dq), dk_loc=_maxabs(r.dk_loc, dk[:tq]), dv_loc=_maxabs(r.dv_loc, dv[:tq]),
+             dk_recv=_maxabs(r.dk_recv, dk[tq:]), dv_recv=_maxabs(r.dv_recv, dv[tq:]))
+    say(f"[gpu] {key} bwd: " + " ".join(f"{k} {v:.3e}" for k, v in e.items()))
+    assert max(e.values()) <= G_TOL, e
+
+    nan = lambda *sh, dt=torch.float32: torch.full(sh, float("nan"), dtype=dt, device=dev)  # noqa: E731
+    # the partial passes: each against the oracle, in one launch and in two the
+    # same bits, and their merge the two-pass forward's bits
+    parts = []
+    for src, kg, vg, keys in ((0, r.k_loc, r.v_loc, o.q_gpos), (1, r.k_recv, r.v_recv, o.recv_gpos)):
+        op, lp = nan(tq, hq, d), nan(hq, tq)
+        F.fc_attn_fwd_partial(r.v, src, r.q, kg, vg, 0.0, op, lp)
+        Op, Lp = A.attention_fwd(c.cu, o.q_gpos, x["q"], keys, x["k_recv" if src else "k_loc"],
+                                 x["v_recv" if src else "v_loc"])
+        assert _maxabs(op, Op) <= O_TOL and _lse_ok(lp, Lp) <= LSE_TOL
+        parts.append((op, lp))
+    both = [nan(tq, hq, d), nan(hq, tq), nan(tq, hq, d), nan(hq, tq)]
+    F.fc_attn_fwd_partials(r.v, r.q, r.k_loc, r.v_loc, r.k_recv, r.v_recv, 0.0, *both)
+    torch.cuda.synchronize()
+    for a, b in zip((*parts[0], *parts[1]), both):
+        assert torch.equal(a, b)
+    ob, of, lo = nan(tq, hq, d, dt=torch.bfloat16), nan(tq, hq, d), nan(hq, tq)
+    F.fc_lse_merge(*parts[0], *parts[1], ob, of, lo)
+    torch.cuda.synchronize()
+    assert torch.equal(ob, r.o) and torch.equal(of, r.o32) and torch.equal(lo, r.lse)
+
+    # without slots behind the tables, and replayed from a graph: the same bits
+    slots = r.v.workspace_size(F.FC_FUSED)[0]
+    again = F.View(case.cu, case.plan, case.cp, case.rank, hq, hkv, d)
+    tables = i["meta_bytes"] - slots
+    buf = torch.empty(tables + 256, dtype=torch.uint8, device=dev)
+    at = buf.data_ptr() + (-buf.data_ptr()) % 256
+    assert F.lib().fc_view_bind(again.handle, at, tables - 1, F._stream()) == -5
+    assert F.lib().fc_view_bind(again.handle, at, tables, F._stream()) == 0
+    seq = [nan(tq, hq, d), nan(hq, tq), nan(tq, hq, d), nan(hq, tq)]
+    F.fc_attn_fwd_partials(again, r.q, r.k_loc, r.v_loc, r.k_recv, r.v_recv, 0.0, *seq)
+    one = [nan(tq, hq, d), nan(hq, tq), nan(tq, hq, d), nan(hq, tq)]
+    F.fc_attn_fwd_partial(again, 0, r.q, r.k_loc, r.v_loc, 0.0, *one[:2])
+    F.fc_attn_fwd_partial(again, 1, r.q, r.k_recv, r.v_recv, 0.0, *one[2:])
+    graph, cap = torch.cuda.CUDAGraph(), [nan(tq, hq, d), nan(hq, tq), nan(tq, hq, d), nan(hq, tq)]
+    with torch.cuda.graph(graph):
+        F.fc_attn_fwd_partials(r.v, r.q, r.k_loc, r.v_loc, r.k_recv, r.v_recv, 0.0, *cap)
+    for _ in range(3):
+        for t in cap:
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b, c1, c2 in zip(both, seq, one, cap):
+            assert torch.equal(a, b) and torch.equal(a, c1) and torch.equal(a, c2)
+    again.close()
+
+    # the partial passes on two streams at once, twice each: uses of the slots
+    # follow one another
+    side = [torch.cuda.Stream(), torch.cuda.Stream()]
+    outs = [[nan(tq, hq, d), nan(hq, tq), nan(tq, hq, d), nan(hq, tq)] for _ in range(4)]
+    torch.cuda.synchronize()
+    for k, o4 in enumerate(outs):
+        with torch.cuda.stream(side[k % 2]):
+            F.fc_attn_fwd_partials(r.v, r.q, r.k_loc, r.v_loc, r.k_recv, r.v_recv, 0.0, *o4)
+    torch.cuda.synchronize()
+    for o4 in outs:
+        for a, b in zip(both, o4):
+            assert torch.equal(a, b)
+
+    # the fused forward, with its workspace and (one pass, unsplit) without
+    for ws in (torch.empty(r.v.workspace_size(F.FC_FUSED)[0], dtype=torch.uint8, device=dev), None):
+        ob, of, lo = nan(tq, hq, d, dt=torch.bfloat16), nan(tq, hq, d), nan(hq, tq)
+        F.fc_attn_fwd(r.v, r.q, r.k_loc, r.v_loc, r.k_recv, r.v_recv, 0.0, F.FC_FUSED, ob, of, lo, ws)
+        torch.cuda.synchronize()
+        assert max(_maxabs(ob, O), _maxabs(of, O)) <= O_TOL and _lse_ok(lo, L) <= LSE_TOL
+
+    # the backward pass with a workspace for split key tiles alone, and the dQ
+    # pass: dK/dV the same bits, dQ the same sums in another order
+    delta = torch.empty_like(r.lse)
+    F.fc_bwd_preprocess(r.v, None, r.do, delta, o_f32=r.o32)
+    part = 2 * i["n_bwd_slots"] * hkv * 128 * d * 4
+    out = r.bwd_outputs()
+    F.fc_attn_bwd_pass(r.v, r.q, r.k_loc, r.v_loc, r.k_recv, r.v_recv, r.lse, delta, r.do, 0.0, *out,
+                       torch.empty(max(part, 1), dtype=torch.uint8, device=dev))
+    alone = nan(tq, hq, d)
+    F.fc_attn_bwd_dq(r.v, r.q, r.k_loc, r.v_loc, r.k_recv, r.v_recv, r.lse, delta, r.do, 0.0, alone)
+    torch.cuda.synchronize()
+    for a, b in zip(out[1:], (r.dk_loc, r.dv_loc, r.dk_recv, r.dv_recv)):
+        assert torch.equal(a, b)
+    assert torch.equal(out[0], alone)
+    assert _maxabs(out[0], r.dq.cpu()) <= ORDER_TOL * float(r.dq.abs().max())
+    # and the same bits on a second run
+    again = Run(case, dev)
+    for n in ("o", "o32", "lse", "dq", "dk_loc", "dv_loc"):
+        assert torch.equal(getattr(again, n), getattr(r, n)), n
+    r.v.close()
+    again.v.close()
