@@ -81,24 +81,24 @@ def lib():
             raise FileNotFoundError(f"{_LIB_PATH} is not built; run python -m paper_2606_08476_amd.build")
         L = C.CDLL(_LIB_PATH)
         sig = {
-            "fc_plan_per_doc": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.POINTER(C.c_int64)],
-            "fc_plan_per_seq": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.POINTER(C.c_int64)],
-            "fc_plan_whole_lpt": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.POINTER(C.c_int64)],
-            "fc_plan_hybrid": [I32P, C.c_int32, C.c_int32, C.c_double, C.POINTER(Shard), C.c_int64,
-                               C.POINTER(C.c_int64), C.POINTER(C.c_uint8)],
-            "fc_plan_validate": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.c_int32],
-            "fc_plan_stats": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.c_int32, C.c_int32,
-                              C.POINTER(C.c_int64), I32P, I32P, C.POINTER(C.c_int64), C.POINTER(C.c_int64),
-                              C.POINTER(C.c_double)],
-            "fc_view_create": [I32P, C.c_int32, C.POINTER(Shard), C.c_int64, C.c_int32, C.c_int32,
-                               C.c_int32, C.c_int32, C.c_int32, C.POINTER(TileCfg), C.POINTER(P)],
-            "fc_view_get_info": [P, C.POINTER(ViewInfo)],
-            "fc_view_export": [P] + [I32P] * 11,
+            "fc_plan_per_doc": [P, C.c_int32, C.c_int32, P, C.c_int64, P],
+            "fc_plan_per_seq": [P, C.c_int32, C.c_int32, P, C.c_int64, P],
+            "fc_plan_whole_lpt": [P, C.c_int32, C.c_int32, P, C.c_int64, P],
+            "fc_plan_hybrid": [P, C.c_int32, C.c_int32, C.c_double, P, C.c_int64,
+                               P, P],
+            "fc_plan_validate": [P, C.c_int32, C.c_int32, P, C.c_int64, C.c_int32],
+            "fc_plan_stats": [P, C.c_int32, C.c_int32, P, C.c_int64, C.c_int32, C.c_int32,
+                              P, P, P, P, P,
+                              P],
+            "fc_view_create": [P, C.c_int32, P, C.c_int64, C.c_int32, C.c_int32,
+                               C.c_int32, C.c_int32, C.c_int32, P, P],
+            "fc_view_get_info": [P, P],
+            "fc_view_export": [P] + [P] * 11,
             "fc_view_bind": [P, P, C.c_size_t, P],
-            "fc_view_export_launch": [P] + [I32P] * 6,
-            "fc_view_export_split": [P] + [I32P] * 5,
-            "fc_workspace_size": [P, C.c_int32, C.POINTER(C.c_size_t), C.POINTER(C.c_size_t),
-                                  C.POINTER(C.c_size_t)],
+            "fc_view_export_launch": [P] + [P] * 6,
+            "fc_view_export_split": [P] + [P] * 5,
+            "fc_workspace_size": [P, C.c_int32, P, P,
+                                  P],
             "fc_kv_gather": [P, P, P, C.c_int64, P, P, P, P, P],
             "fc_attn_fwd": [P, P, P, P, P, P, C.c_float, C.c_int32, P, P, P, P, C.c_size_t, P],
             "fc_attn_fwd_partial": [P, C.c_int32, P, P, P, C.c_float, P, P, P],
@@ -133,28 +133,28 @@ def _check(rc: int):
 
 def _cu(cu):
     a = np.ascontiguousarray(np.asarray(cu, dtype=np.int32))
-    return a, a.ctypes.data_as(I32P), int(a.size - 1)
+    return a, a.ctypes.data, int(a.size - 1)
 
 
 def _shards(plan):
+    """The plan as an int32 [n, 4] array (the layout of fc_shard; keep it alive
+    during the call), its address and n. (Addresses of numpy arrays
+    throughout: an array type made per call, Shard * n, costs some 50 us.)"""
     plan = np.ascontiguousarray(np.asarray(plan, dtype=np.int32).reshape(-1, 4))
-    arr = (Shard * max(1, len(plan)))()
-    C.memmove(arr, plan.ctypes.data, plan.nbytes)
-    return arr, len(plan)
+    return plan, plan.ctypes.data, len(plan)
 
 
 def _plan_out(fn, *args):
     n = C.c_int64(0)
     cap = 1024
     while True:
-        buf = (Shard * cap)()
-        rc = fn(*args, buf, cap, C.byref(n))
+        buf = np.empty((cap, 4), dtype=np.int32)
+        rc = fn(*args, buf.ctypes.data, cap, C.byref(n))
         if rc == -7:
             cap = int(n.value)
             continue
         _check(rc)
-        out = np.frombuffer(buf, dtype=np.int32, count=4 * n.value).reshape(-1, 4).copy()
-        return out
+        return buf[:n.value].copy()
 
 
 # ------------------------------------------------------------------ planners
@@ -176,36 +176,35 @@ def fc_plan_whole_lpt(cu, cp: int) -> np.ndarray:
 
 def fc_plan_hybrid(cu, cp: int, target_r: float = 1.05):
     a, p, n = _cu(cu)
-    isp = (C.c_uint8 * n)()
+    isp = np.zeros(n, dtype=np.uint8)
     cnt = C.c_int64(0)
     cap = 4 * n + 4 * cp + 16
     while True:
-        buf = (Shard * cap)()
-        rc = lib().fc_plan_hybrid(p, n, cp, float(target_r), buf, cap, C.byref(cnt), isp)
+        buf = np.empty((cap, 4), dtype=np.int32)
+        rc = lib().fc_plan_hybrid(p, n, cp, float(target_r), buf.ctypes.data, cap, C.byref(cnt),
+                                  isp.ctypes.data)
         if rc == -7:
             cap = int(cnt.value)
             continue
         _check(rc)
-        plan = np.frombuffer(buf, dtype=np.int32, count=4 * cnt.value).reshape(-1, 4).copy()
-        return plan, np.frombuffer(isp, dtype=np.uint8).copy()
+        return buf[:cnt.value].copy(), isp
 
 
 def fc_plan_validate(cu, cp: int, plan, require_equal_tokens: bool = False) -> None:
     a, p, n = _cu(cu)
-    s, m = _shards(plan)
-    _check(lib().fc_plan_validate(p, n, cp, s, m, int(bool(require_equal_tokens))))
+    s, sp, m = _shards(plan)
+    _check(lib().fc_plan_validate(p, n, cp, sp, m, int(bool(require_equal_tokens))))
 
 
 def fc_plan_stats(cu, cp: int, plan, hkv: int, d: int) -> dict:
     a, p, n = _cu(cu)
-    s, m = _shards(plan)
-    work = (C.c_int64 * cp)()
-    tok = (C.c_int32 * cp)()
-    rcv = (C.c_int32 * cp)()
+    s, sp, m = _shards(plan)
+    work = np.zeros(cp, dtype=np.int64)
+    tok, rcv = np.zeros(cp, dtype=np.int32), np.zeros(cp, dtype=np.int32)
     eq4, eq5, imb = C.c_int64(0), C.c_int64(0), C.c_double(0)
-    _check(lib().fc_plan_stats(p, n, cp, s, m, hkv, d, work, tok, rcv, C.byref(eq4), C.byref(eq5),
-                               C.byref(imb)))
-    return dict(work=list(work), tokens=list(tok), recv_tokens=list(rcv), eq4=eq4.value,
+    _check(lib().fc_plan_stats(p, n, cp, sp, m, hkv, d, work.ctypes.data, tok.ctypes.data,
+                               rcv.ctypes.data, C.byref(eq4), C.byref(eq5), C.byref(imb)))
+    return dict(work=work.tolist(), tokens=tok.tolist(), recv_tokens=rcv.tolist(), eq4=eq4.value,
                 eq5=eq5.value, imbalance=imb.value)
 
 
@@ -219,15 +218,26 @@ class View:
 
     def __init__(self, cu, plan, cp: int, rank: int, hq: int, hkv: int, d: int, tiles=None):
         a, p, n = _cu(cu)
-        s, m = _shards(plan)
+        s, sp, m = _shards(plan)
         h = P()
         t = C.byref(TileCfg(*[int(x) for x in tiles])) if tiles is not None else None
-        _check(lib().fc_view_create(p, n, s, m, cp, rank, hq, hkv, d, t, C.byref(h)))
+        _check(lib().fc_view_create(p, n, sp, m, cp, rank, hq, hkv, d, t, C.byref(h)))
         self._h = h
         self.meta = None
         info = ViewInfo()
         _check(lib().fc_view_get_info(self._h, C.byref(info)))
-        self.info = info.as_dict()
+        self._info = info
+        # shapes every device call checks its tensors against
+        tq, tr, hq, hkv, d = info.t_q, info.t_recv, info.hq, info.hkv, info.d
+        self._q, self._kv, self._kvr, self._l = (tq, hq, d), (tq, hkv, d), (tr, hkv, d), (hq, tq)
+
+    @property
+    def info(self) -> dict:
+        """The fields of fc_view_info."""
+        d = self.__dict__.get("_info_dict")
+        if d is None:
+            d = self._info_dict = self._info.as_dict()
+        return d
 
     @property
     def handle(self):
@@ -277,9 +287,9 @@ class View:
     def bind(self, device="cuda", buf=None):
         """Upload the view's tables on the current stream into ``buf`` (a
         uint8 device tensor, allocated here if not given) and keep it."""
-        import torch
-        nbytes = int(self.info["meta_bytes"])
+        nbytes = self._info.meta_bytes
         if buf is None:
+            _load_torch()
             buf = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
         off = (-buf.data_ptr()) % 256
         if not buf.is_cuda or buf.numel() - off < nbytes:
@@ -306,110 +316,126 @@ class View:
             pass
 
 
+# torch, loaded by the first call that needs it (the planners and views do not)
+torch = _Tensor = _raw_stream = BF = F32 = None
+
+
+def _load_torch():
+    global torch, _Tensor, _raw_stream, BF, F32
+    if torch is None:
+        import torch as t
+        _Tensor, BF, F32 = t.Tensor, t.bfloat16, t.float32
+        # the current stream's handle without a Stream object, where torch has it
+        raw, dev = getattr(t._C, "_cuda_getCurrentRawStream", None), getattr(t._C, "_cuda_getDevice", None)
+        if raw is not None and dev is not None:
+            _raw_stream = lambda: raw(dev())  # noqa: E731
+        else:
+            _raw_stream = lambda: t.cuda.current_stream().cuda_stream  # noqa: E731
+        torch = t
+
+
 def _stream():
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+    if torch is None:
+        _load_torch()
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return _raw_stream()
 
 
 def _ptr(t, shape, dtype, name):
-    import torch
+    """Device address of tensor `t` after checking it; None for None."""
     if t is None:
         return None
-    if not isinstance(t, torch.Tensor) or not t.is_cuda:
+    if (isinstance(t, _Tensor) and t.dtype is dtype and t.shape == shape and t.is_cuda
+            and t.is_contiguous()):
+        return t.data_ptr()
+    if not isinstance(t, _Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if tuple(t.shape) != tuple(shape):
         raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
-    if not t.is_contiguous():
-        raise ValueError(f"{name} must be contiguous")
-    return t.data_ptr()
+    raise ValueError(f"{name} must be contiguous")
 
 
 def fc_kv_gather(view: View, k_packed, v_packed, k_loc, v_loc, k_recv, v_recv):
-    import torch
-    i = view.info
+    if torch is None:
+        _load_torch()
+    KV, KR = view._kv, view._kvr
     T = k_packed.shape[0]
-    bf = torch.bfloat16
-    args = [_ptr(k_packed, (T, i["hkv"], i["d"]), bf, "k_packed"),
-            _ptr(v_packed, (T, i["hkv"], i["d"]), bf, "v_packed"), T,
-            _ptr(k_loc, (i["t_q"], i["hkv"], i["d"]), bf, "k_loc"),
-            _ptr(v_loc, (i["t_q"], i["hkv"], i["d"]), bf, "v_loc"),
-            _ptr(k_recv, (i["t_recv"], i["hkv"], i["d"]), bf, "k_recv"),
-            _ptr(v_recv, (i["t_recv"], i["hkv"], i["d"]), bf, "v_recv")]
-    _check(lib().fc_kv_gather(view.handle, *args, _stream()))
+    packed = (T, KV[1], KV[2])
+    _check(lib().fc_kv_gather(
+        view.handle, _ptr(k_packed, packed, BF, "k_packed"), _ptr(v_packed, packed, BF, "v_packed"), T,
+        _ptr(k_loc, KV, BF, "k_loc"), _ptr(v_loc, KV, BF, "v_loc"), _ptr(k_recv, KR, BF, "k_recv"),
+        _ptr(v_recv, KR, BF, "v_recv"), _stream()))
 
 
 def fc_attn_fwd(view: View, q, k_loc, v_loc, k_recv, v_recv, scale, mode, o, o_f32, lse, ws):
-    import torch
-    i = view.info
-    bf, f32 = torch.bfloat16, torch.float32
-    tq, tr, hq, hkv, d = i["t_q"], i["t_recv"], i["hq"], i["hkv"], i["d"]
+    if torch is None:
+        _load_torch()
+    Q, KV, KR, L = view._q, view._kv, view._kvr, view._l
     ws_ptr = ws.data_ptr() if ws is not None and ws.numel() else None
     ws_bytes = ws.numel() * ws.element_size() if ws is not None else 0
     _check(lib().fc_attn_fwd(
-        view.handle, _ptr(q, (tq, hq, d), bf, "q"), _ptr(k_loc, (tq, hkv, d), bf, "k_loc"),
-        _ptr(v_loc, (tq, hkv, d), bf, "v_loc"), _ptr(k_recv, (tr, hkv, d), bf, "k_recv"),
-        _ptr(v_recv, (tr, hkv, d), bf, "v_recv"), float(scale), int(mode),
-        _ptr(o, (tq, hq, d), bf, "o"), _ptr(o_f32, (tq, hq, d), f32, "o_f32"),
-        _ptr(lse, (hq, tq), f32, "lse"), ws_ptr, ws_bytes, _stream()))
+        view.handle, _ptr(q, Q, BF, "q"), _ptr(k_loc, KV, BF, "k_loc"),
+        _ptr(v_loc, KV, BF, "v_loc"), _ptr(k_recv, KR, BF, "k_recv"),
+        _ptr(v_recv, KR, BF, "v_recv"), float(scale), int(mode),
+        _ptr(o, Q, BF, "o"), _ptr(o_f32, Q, F32, "o_f32"),
+        _ptr(lse, L, F32, "lse"), ws_ptr, ws_bytes, _stream()))
 
 
 def fc_attn_fwd_partial(view: View, src, q, k_src, v_src, scale, o_part, lse_part):
-    import torch
-    i = view.info
-    bf, f32 = torch.bfloat16, torch.float32
-    tq, hq, hkv, d = i["t_q"], i["hq"], i["hkv"], i["d"]
-    tk = tq if src == 0 else i["t_recv"]
+    if torch is None:
+        _load_torch()
+    Q, KV, KR, L = view._q, view._kv, view._kvr, view._l
+    K = KV if src == 0 else KR
     _check(lib().fc_attn_fwd_partial(
-        view.handle, int(src), _ptr(q, (tq, hq, d), bf, "q"), _ptr(k_src, (tk, hkv, d), bf, "k_src"),
-        _ptr(v_src, (tk, hkv, d), bf, "v_src"), float(scale), _ptr(o_part, (tq, hq, d), f32, "o_part"),
-        _ptr(lse_part, (hq, tq), f32, "lse_part"), _stream()))
+        view.handle, int(src), _ptr(q, Q, BF, "q"), _ptr(k_src, K, BF, "k_src"),
+        _ptr(v_src, K, BF, "v_src"), float(scale), _ptr(o_part, Q, F32, "o_part"),
+        _ptr(lse_part, L, F32, "lse_part"), _stream()))
 
 
 def fc_attn_fwd_partials(view: View, q, k_loc, v_loc, k_recv, v_recv, scale, o_loc, lse_loc,
                          o_recv, lse_recv):
-    import torch
-    i = view.info
-    bf, f32 = torch.bfloat16, torch.float32
-    tq, tr, hq, hkv, d = i["t_q"], i["t_recv"], i["hq"], i["hkv"], i["d"]
+    if torch is None:
+        _load_torch()
+    Q, KV, KR, L = view._q, view._kv, view._kvr, view._l
     _check(lib().fc_attn_fwd_partials(
-        view.handle, _ptr(q, (tq, hq, d), bf, "q"), _ptr(k_loc, (tq, hkv, d), bf, "k_loc"),
-        _ptr(v_loc, (tq, hkv, d), bf, "v_loc"), _ptr(k_recv, (tr, hkv, d), bf, "k_recv"),
-        _ptr(v_recv, (tr, hkv, d), bf, "v_recv"), float(scale),
-        _ptr(o_loc, (tq, hq, d), f32, "o_loc"), _ptr(lse_loc, (hq, tq), f32, "lse_loc"),
-        _ptr(o_recv, (tq, hq, d), f32, "o_recv"), _ptr(lse_recv, (hq, tq), f32, "lse_recv"),
+        view.handle, _ptr(q, Q, BF, "q"), _ptr(k_loc, KV, BF, "k_loc"),
+        _ptr(v_loc, KV, BF, "v_loc"), _ptr(k_recv, KR, BF, "k_recv"),
+        _ptr(v_recv, KR, BF, "v_recv"), float(scale),
+        _ptr(o_loc, Q, F32, "o_loc"), _ptr(lse_loc, L, F32, "lse_loc"),
+        _ptr(o_recv, Q, F32, "o_recv"), _ptr(lse_recv, L, F32, "lse_recv"),
         _stream()))
 
 
 def fc_lse_merge(o_a, lse_a, o_b, lse_b, o_bf16, o_f32, lse_out):
-    import torch
+    if torch is None:
+        _load_torch()
     t, h, d = o_a.shape
-    f32, bf = torch.float32, torch.bfloat16
     _check(lib().fc_lse_merge(
-        _ptr(o_a, (t, h, d), f32, "o_a"), _ptr(lse_a, (h, t), f32, "lse_a"),
-        _ptr(o_b, (t, h, d), f32, "o_b"), _ptr(lse_b, (h, t), f32, "lse_b"), t, h, d,
-        _ptr(o_bf16, (t, h, d), bf, "o_bf16"), _ptr(o_f32, (t, h, d), f32, "o_f32"),
-        _ptr(lse_out, (h, t), f32, "lse_out"), _stream()))
+        _ptr(o_a, (t, h, d), F32, "o_a"), _ptr(lse_a, (h, t), F32, "lse_a"),
+        _ptr(o_b, (t, h, d), F32, "o_b"), _ptr(lse_b, (h, t), F32, "lse_b"), t, h, d,
+        _ptr(o_bf16, (t, h, d), BF, "o_bf16"), _ptr(o_f32, (t, h, d), F32, "o_f32"),
+        _ptr(lse_out, (h, t), F32, "lse_out"), _stream()))
 
 
 def fc_attn_bwd(view: View, q, k_loc, v_loc, k_recv, v_recv, o, lse, dout, scale,
                 dq, dk_loc, dv_loc, dk_recv, dv_recv, ws, deterministic: bool = True, o_f32=None):
     """o: the forward's bf16 output; o_f32 (optional): its fp32 output, from
     which delta is then computed (o may be None)."""
-    import torch
-    i = view.info
-    bf, f32 = torch.bfloat16, torch.float32
-    tq, tr, hq, hkv, d = i["t_q"], i["t_recv"], i["hq"], i["hkv"], i["d"]
+    if torch is None:
+        _load_torch()
+    Q, KV, KR, L = view._q, view._kv, view._kvr, view._l
     _check(lib().fc_attn_bwd(
-        view.handle, _ptr(q, (tq, hq, d), bf, "q"), _ptr(k_loc, (tq, hkv, d), bf, "k_loc"),
-        _ptr(v_loc, (tq, hkv, d), bf, "v_loc"), _ptr(k_recv, (tr, hkv, d), bf, "k_recv"),
-        _ptr(v_recv, (tr, hkv, d), bf, "v_recv"), _ptr(o, (tq, hq, d), bf, "o"),
-        _ptr(o_f32, (tq, hq, d), f32, "o_f32"), _ptr(lse, (hq, tq), f32, "lse"), _ptr(dout, (tq, hq, d), bf, "dout"), float(scale),
+        view.handle, _ptr(q, Q, BF, "q"), _ptr(k_loc, KV, BF, "k_loc"),
+        _ptr(v_loc, KV, BF, "v_loc"), _ptr(k_recv, KR, BF, "k_recv"),
+        _ptr(v_recv, KR, BF, "v_recv"), _ptr(o, Q, BF, "o"),
+        _ptr(o_f32, Q, F32, "o_f32"), _ptr(lse, L, F32, "lse"), _ptr(dout, Q, BF, "dout"), float(scale),
         int(bool(deterministic)),
-        _ptr(dq, (tq, hq, d), f32, "dq"), _ptr(dk_loc, (tq, hkv, d), f32, "dk_loc"),
-        _ptr(dv_loc, (tq, hkv, d), f32, "dv_loc"), _ptr(dk_recv, (tr, hkv, d), f32, "dk_recv"),
-        _ptr(dv_recv, (tr, hkv, d), f32, "dv_recv"), ws.data_ptr(), ws.numel() * ws.element_size(),
+        _ptr(dq, Q, F32, "dq"), _ptr(dk_loc, KV, F32, "dk_loc"),
+        _ptr(dv_loc, KV, F32, "dv_loc"), _ptr(dk_recv, KR, F32, "dk_recv"),
+        _ptr(dv_recv, KR, F32, "dv_recv"), ws.data_ptr(), ws.numel() * ws.element_size(),
         _stream()))
 
 
@@ -418,31 +444,30 @@ def fc_attn_bwd_noalloc(view: View, q, k_loc, v_loc, k_recv, v_recv, o, lse, dou
                         o_f32=None):
     """fc_attn_bwd with its workspace in the library's static device scratch
     (no device allocation)."""
-    import torch
-    i = view.info
-    bf, f32 = torch.bfloat16, torch.float32
-    tq, tr, hq, hkv, d = i["t_q"], i["t_recv"], i["hq"], i["hkv"], i["d"]
+    if torch is None:
+        _load_torch()
+    Q, KV, KR, L = view._q, view._kv, view._kvr, view._l
     _check(lib().fc_attn_bwd_noalloc(
-        view.handle, _ptr(q, (tq, hq, d), bf, "q"), _ptr(k_loc, (tq, hkv, d), bf, "k_loc"),
-        _ptr(v_loc, (tq, hkv, d), bf, "v_loc"), _ptr(k_recv, (tr, hkv, d), bf, "k_recv"),
-        _ptr(v_recv, (tr, hkv, d), bf, "v_recv"), _ptr(o, (tq, hq, d), bf, "o"),
-        _ptr(o_f32, (tq, hq, d), f32, "o_f32"), _ptr(lse, (hq, tq), f32, "lse"), _ptr(dout, (tq, hq, d), bf, "dout"), float(scale),
+        view.handle, _ptr(q, Q, BF, "q"), _ptr(k_loc, KV, BF, "k_loc"),
+        _ptr(v_loc, KV, BF, "v_loc"), _ptr(k_recv, KR, BF, "k_recv"),
+        _ptr(v_recv, KR, BF, "v_recv"), _ptr(o, Q, BF, "o"),
+        _ptr(o_f32, Q, F32, "o_f32"), _ptr(lse, L, F32, "lse"), _ptr(dout, Q, BF, "dout"), float(scale),
         int(bool(deterministic)),
-        _ptr(dq, (tq, hq, d), f32, "dq"), _ptr(dk_loc, (tq, hkv, d), f32, "dk_loc"),
-        _ptr(dv_loc, (tq, hkv, d), f32, "dv_loc"), _ptr(dk_recv, (tr, hkv, d), f32, "dk_recv"),
-        _ptr(dv_recv, (tr, hkv, d), f32, "dv_recv"), _stream()))
+        _ptr(dq, Q, F32, "dq"), _ptr(dk_loc, KV, F32, "dk_loc"),
+        _ptr(dv_loc, KV, F32, "dv_loc"), _ptr(dk_recv, KR, F32, "dk_recv"),
+        _ptr(dv_recv, KR, F32, "dv_recv"), _stream()))
 
 
 def fc_bwd_preprocess(view: View, o, dout, delta, o_f32=None):
     """delta from the bf16 o, or from o_f32 when given (o may then be None)."""
-    import torch
-    i = view.info
-    tq, hq, d = i["t_q"], i["hq"], i["d"]
+    if torch is None:
+        _load_torch()
+    Q, KV, KR, L = view._q, view._kv, view._kvr, view._l
     _check(lib().fc_bwd_preprocess(
-        view.handle, _ptr(o, (tq, hq, d), torch.bfloat16, "o"),
-        _ptr(o_f32, (tq, hq, d), torch.float32, "o_f32"),
-        _ptr(dout, (tq, hq, d), torch.bfloat16, "dout"),
-        _ptr(delta, (hq, tq), torch.float32, "delta"), _stream()))
+        view.handle, _ptr(o, Q, BF, "o"),
+        _ptr(o_f32, Q, F32, "o_f32"),
+        _ptr(dout, Q, BF, "dout"),
+        _ptr(delta, L, F32, "delta"), _stream()))
 
 
 def _ws(ws):
@@ -453,45 +478,42 @@ def _ws(ws):
 
 def fc_attn_bwd_pass(view: View, q, k_loc, v_loc, k_recv, v_recv, lse, delta, dout, scale,
                      dq, dk_loc, dv_loc, dk_recv, dv_recv, ws=None, deterministic: bool = True):
-    import torch
-    i = view.info
-    bf, f32 = torch.bfloat16, torch.float32
-    tq, tr, hq, hkv, d = i["t_q"], i["t_recv"], i["hq"], i["hkv"], i["d"]
+    if torch is None:
+        _load_torch()
+    Q, KV, KR, L = view._q, view._kv, view._kvr, view._l
     _check(lib().fc_attn_bwd_pass(
-        view.handle, _ptr(q, (tq, hq, d), bf, "q"), _ptr(k_loc, (tq, hkv, d), bf, "k_loc"),
-        _ptr(v_loc, (tq, hkv, d), bf, "v_loc"), _ptr(k_recv, (tr, hkv, d), bf, "k_recv"),
-        _ptr(v_recv, (tr, hkv, d), bf, "v_recv"), _ptr(lse, (hq, tq), f32, "lse"),
-        _ptr(delta, (hq, tq), f32, "delta"), _ptr(dout, (tq, hq, d), bf, "dout"), float(scale),
+        view.handle, _ptr(q, Q, BF, "q"), _ptr(k_loc, KV, BF, "k_loc"),
+        _ptr(v_loc, KV, BF, "v_loc"), _ptr(k_recv, KR, BF, "k_recv"),
+        _ptr(v_recv, KR, BF, "v_recv"), _ptr(lse, L, F32, "lse"),
+        _ptr(delta, L, F32, "delta"), _ptr(dout, Q, BF, "dout"), float(scale),
         int(bool(deterministic)),
-        _ptr(dq, (tq, hq, d), f32, "dq"), _ptr(dk_loc, (tq, hkv, d), f32, "dk_loc"),
-        _ptr(dv_loc, (tq, hkv, d), f32, "dv_loc"), _ptr(dk_recv, (tr, hkv, d), f32, "dk_recv"),
-        _ptr(dv_recv, (tr, hkv, d), f32, "dv_recv"), *_ws(ws), _stream()))
+        _ptr(dq, Q, F32, "dq"), _ptr(dk_loc, KV, F32, "dk_loc"),
+        _ptr(dv_loc, KV, F32, "dv_loc"), _ptr(dk_recv, KR, F32, "dk_recv"),
+        _ptr(dv_recv, KR, F32, "dv_recv"), *_ws(ws), _stream()))
 
 
 def fc_attn_bwd_dkdv(view: View, q, k_loc, v_loc, k_recv, v_recv, lse, delta, dout, scale,
                      dk_loc, dv_loc, dk_recv, dv_recv, ws=None):
-    import torch
-    i = view.info
-    bf, f32 = torch.bfloat16, torch.float32
-    tq, tr, hq, hkv, d = i["t_q"], i["t_recv"], i["hq"], i["hkv"], i["d"]
+    if torch is None:
+        _load_torch()
+    Q, KV, KR, L = view._q, view._kv, view._kvr, view._l
     _check(lib().fc_attn_bwd_dkdv(
-        view.handle, _ptr(q, (tq, hq, d), bf, "q"), _ptr(k_loc, (tq, hkv, d), bf, "k_loc"),
-        _ptr(v_loc, (tq, hkv, d), bf, "v_loc"), _ptr(k_recv, (tr, hkv, d), bf, "k_recv"),
-        _ptr(v_recv, (tr, hkv, d), bf, "v_recv"), _ptr(lse, (hq, tq), f32, "lse"),
-        _ptr(delta, (hq, tq), f32, "delta"), _ptr(dout, (tq, hq, d), bf, "dout"), float(scale),
-        _ptr(dk_loc, (tq, hkv, d), f32, "dk_loc"), _ptr(dv_loc, (tq, hkv, d), f32, "dv_loc"),
-        _ptr(dk_recv, (tr, hkv, d), f32, "dk_recv"), _ptr(dv_recv, (tr, hkv, d), f32, "dv_recv"),
+        view.handle, _ptr(q, Q, BF, "q"), _ptr(k_loc, KV, BF, "k_loc"),
+        _ptr(v_loc, KV, BF, "v_loc"), _ptr(k_recv, KR, BF, "k_recv"),
+        _ptr(v_recv, KR, BF, "v_recv"), _ptr(lse, L, F32, "lse"),
+        _ptr(delta, L, F32, "delta"), _ptr(dout, Q, BF, "dout"), float(scale),
+        _ptr(dk_loc, KV, F32, "dk_loc"), _ptr(dv_loc, KV, F32, "dv_loc"),
+        _ptr(dk_recv, KR, F32, "dk_recv"), _ptr(dv_recv, KR, F32, "dv_recv"),
         *_ws(ws), _stream()))
 
 
 def fc_attn_bwd_dq(view: View, q, k_loc, v_loc, k_recv, v_recv, lse, delta, dout, scale, dq):
-    import torch
-    i = view.info
-    bf, f32 = torch.bfloat16, torch.float32
-    tq, tr, hq, hkv, d = i["t_q"], i["t_recv"], i["hq"], i["hkv"], i["d"]
+    if torch is None:
+        _load_torch()
+    Q, KV, KR, L = view._q, view._kv, view._kvr, view._l
     _check(lib().fc_attn_bwd_dq(
-        view.handle, _ptr(q, (tq, hq, d), bf, "q"), _ptr(k_loc, (tq, hkv, d), bf, "k_loc"),
-        _ptr(v_loc, (tq, hkv, d), bf, "v_loc"), _ptr(k_recv, (tr, hkv, d), bf, "k_recv"),
-        _ptr(v_recv, (tr, hkv, d), bf, "v_recv"), _ptr(lse, (hq, tq), f32, "lse"),
-        _ptr(delta, (hq, tq), f32, "delta"), _ptr(dout, (tq, hq, d), bf, "dout"), float(scale),
-        _ptr(dq, (tq, hq, d), f32, "dq"), _stream()))
+        view.handle, _ptr(q, Q, BF, "q"), _ptr(k_loc, KV, BF, "k_loc"),
+        _ptr(v_loc, KV, BF, "v_loc"), _ptr(k_recv, KR, BF, "k_recv"),
+        _ptr(v_recv, KR, BF, "v_recv"), _ptr(lse, L, F32, "lse"),
+        _ptr(delta, L, F32, "delta"), _ptr(dout, Q, BF, "dout"), float(scale),
+        _ptr(dq, Q, F32, "dq"), _stream()))
