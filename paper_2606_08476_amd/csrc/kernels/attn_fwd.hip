@@ -541,61 +541,59 @@ __global__ __launch_bounds__(256, 2) void attn_fwd_kernel(FwdParams p) {
 
 // The chunks of a split view's query tiles, merged: a source's chunks in key
 // order, then (FINAL) the local with the received partial, as the merge kernel
-// would, or each source's partial by itself. One wave per workgroup, for one wave's 32 rows of an entry (q0 q1 first-slot
-// received-chunks local-chunks 0 0 0). Bound by the latency of its reads (a
-// chunk's slot is read while the one before is merged).
+// would, or each source's partial by itself. A workgroup takes one wave's 32
+// rows of an entry (q0 q1 first-slot received-chunks local-chunks 0 0 0), a
+// quarter of the columns per wave and four chunks in flight at once: bound by
+// the latency of its reads.
 template <int D, int HPW, bool FINAL>
-__global__ __launch_bounds__(64) void fwd_combine_kernel(FwdParams p) {
-  constexpr int RPW = 32 / HPW, NK = D / 8;  // NK: 16-byte pieces per lane
-  __shared__ __attribute__((aligned(16))) char smem[32 * D * 4];
-  const int lane = threadIdx.x, l31 = lane & 31, half = lane >> 5;
-  const int wave = blockIdx.x & 3, b = blockIdx.x >> 2;
+__global__ __launch_bounds__(256) void fwd_combine_kernel(FwdParams p) {
+  constexpr int RPW = 32 / HPW, KW = D / 32;  // KW: 16-byte pieces per lane
+  __shared__ __attribute__((aligned(16))) float st[32 * D];
+  const int lane = threadIdx.x & 63, l31 = lane & 31;
+  const int qw = blockIdx.x & 3, b = blockIdx.x >> 2;  // the rows' wave, the tile
   const int kvh = b % p.hkv, rest = b / p.hkv, hc = rest % p.head_chunks;
   const int32_t* e = p.comb + 8 * (rest / p.head_chunks);
   const int q0 = e[0], q1 = e[1], first = e[2], n_r = e[3], n_l = e[4];
-  if (q0 + wave * RPW >= q1) return;
-  auto slot = [&](int c) { return (size_t(first + c) * p.head_chunks + hc) * p.hkv + kvh; };
-  auto read = [&](f32x4 (&x)[NK], float& l, int c) {
-    const size_t sl = slot(c);
-    const float* const o = p.slots + (sl * 4 + wave) * (32 * D) + 4 * lane;
+  if (q0 + qw * RPW >= q1) return;
+  auto read = [&](f32x4 (&x)[KW], float& l, int c) {
+    const size_t sl = (size_t(first + c) * p.head_chunks + hc) * p.hkv + kvh;
+    const float* const o = p.slots + (sl * 4 + qw) * (32 * D) + 256 * KW * wave_id() + 4 * lane;
 #pragma unroll
-    for (int k = 0; k < NK; ++k) x[k] = *reinterpret_cast<const f32x4*>(o + 256 * k);
-    l = p.slot_lse[sl * 128 + 32 * wave + l31];
+    for (int k = 0; k < KW; ++k) x[k] = *reinterpret_cast<const f32x4*>(o + 256 * k);
+    l = p.slot_lse[sl * 128 + 32 * qw + l31];
   };
-  auto merge = [&](f32x4 (&a)[NK], float& la, const f32x4 (&x)[NK], float lx) {
+  auto merge = [&](f32x4 (&a)[KW], float& la, const f32x4 (&x)[KW], float lx) {
     const Merge2 w = merge2(la, lx);
     la = w.lse;
 #pragma unroll
-    for (int k = 0; k < NK; ++k)
+    for (int k = 0; k < KW; ++k)
 #pragma unroll
       for (int j = 0; j < 4; ++j) a[k][j] = merge2_value(w, a[k][j], x[k][j]);
   };
-  // chunks c0 .. c1-1 of one source, each read while the one before is merged
-  auto source = [&](f32x4 (&a)[NK], float& la, int c0, int c1) __attribute__((always_inline)) {
-    f32x4 x[NK], y[NK];
-    float lx = 0.f, ly = 0.f;
+  // chunks c0 .. c1-1 of one source
+  auto source = [&](f32x4 (&a)[KW], float& la, int c0, int c1) __attribute__((always_inline)) {
+    f32x4 x[4][KW];
+    float lx[4];
     read(a, la, c0);
-    if (c0 + 1 < c1) read(x, lx, c0 + 1);
-    for (int c = c0 + 1; c < c1; c += 2) {
-      if (c + 1 < c1) read(y, ly, c + 1);
-      merge(a, la, x, lx);
-      if (c + 2 < c1) read(x, lx, c + 2);
-      if (c + 1 < c1) merge(a, la, y, ly);
+    for (int c = c0 + 1; c < c1; c += 4) {
+#pragma unroll
+      for (int u = 0; u < 4; ++u) read(x[u], lx[u], min(c + u, c1 - 1));
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (c + u < c1) merge(a, la, x[u], lx[u]);
     }
   };
   const int h0 = kvh * p.group + hc * HPW;
-  auto put = [&](const f32x4 (&a)[NK], float la, float* of, u16* ob, float* lse) {
-    store_rows<D, RPW>(
-        smem, true, [&](int db, int g) { return a[4 * db + g]; }, q0 + wave * RPW, q1, p.hq, h0, of,
-        ob);
-    const int qrow = q0 + wave * RPW + l31 % RPW;
-    if (half == 0 && qrow < q1) lse[(size_t)(h0 + l31 / RPW) * p.t_q + qrow] = la;
+  auto put = [&](const f32x4 (&a)[KW], float la, float* of, u16* ob, float* lse) {
+    store_rows_shared<D, RPW>(st, [&](int k) { return a[k]; }, q0 + qw * RPW, q1, p.hq, h0, of, ob);
+    const int qrow = q0 + qw * RPW + l31 % RPW;
+    if (threadIdx.x < 32 && qrow < q1) lse[(size_t)(h0 + l31 / RPW) * p.t_q + qrow] = la;
   };
-  f32x4 a[NK], r[NK];
+  f32x4 a[KW], r[KW];
   float la = -INFINITY, lr = -INFINITY;
   // (a source with no chunk: an empty partial)
 #pragma unroll
-  for (int k = 0; k < NK; ++k) a[k] = r[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int k = 0; k < KW; ++k) a[k] = r[k] = f32x4{0.f, 0.f, 0.f, 0.f};
   const bool local = FINAL || p.o_f32, recv = FINAL || p.o_f32_recv;
   if (local && n_l > 0) source(a, la, n_r, n_r + n_l);
   if (recv && n_r > 0) source(r, lr, 0, n_r);
@@ -617,9 +615,9 @@ static hipError_t launch_units_t(const FwdParams& p, hipStream_t s) {
   if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
   const dim3 cgrid(unsigned(p.n_comb) * p.hkv * p.head_chunks * 4);
   if (p.o_bf16)
-    hipLaunchKernelGGL((fwd_combine_kernel<D, HPW, true>), cgrid, dim3(64), 0, s, p);
+    hipLaunchKernelGGL((fwd_combine_kernel<D, HPW, true>), cgrid, dim3(256), 0, s, p);
   else
-    hipLaunchKernelGGL((fwd_combine_kernel<D, HPW, false>), cgrid, dim3(64), 0, s, p);
+    hipLaunchKernelGGL((fwd_combine_kernel<D, HPW, false>), cgrid, dim3(256), 0, s, p);
   return hipGetLastError();
 }
 

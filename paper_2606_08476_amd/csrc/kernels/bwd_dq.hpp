@@ -252,60 +252,54 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
 }
 
 // dQ of a query tile whose key range was split: the parts' slots added in
-// slot order (key order), scaled and stored. One wave per workgroup, for one
-// wave's 32 rows, so that few tiles still spread over the chip; two slots are
-// in flight at once. Bound by the latency of its reads.
+// slot order (key order), scaled and stored. A workgroup takes one wave's 32
+// rows, a quarter of the columns per wave and four slots in flight at once, so
+// that few tiles still spread over the chip: bound by the latency of its reads.
 template <int D, int HPW>
-__global__ __launch_bounds__(64) void dq_combine_kernel(DqParams p) {
-  constexpr int RPW = 32 / HPW, DB = D / 32;
-  __shared__ __attribute__((aligned(16))) char smem[32 * D * 4];
-  const int lane = threadIdx.x;
-  const int wave = blockIdx.x & 3, b = blockIdx.x >> 2;
+__global__ __launch_bounds__(256) void dq_combine_kernel(DqParams p) {
+  constexpr int RPW = 32 / HPW, KW = D / 32;  // KW: 16-byte pieces per lane
+  __shared__ __attribute__((aligned(16))) float st[32 * D];
+  const int lane = threadIdx.x & 63;
+  const int qw = blockIdx.x & 3, b = blockIdx.x >> 2;  // the rows' wave, the tile
   const int kvh = b % p.hkv, rest = b / p.hkv, hc = rest % p.head_chunks;
   const int32_t* e = p.comb + 8 * (rest / p.head_chunks);
   const int q0 = e[0], q1 = e[1], first = e[2], n = e[3];
-  if (q0 + wave * RPW >= q1) return;
-  auto at = [&](int s) {
+  if (q0 + qw * RPW >= q1) return;
+  auto read = [&](f32x4 (&x)[KW], int s) {
     const size_t slot = (size_t(first + s) * p.head_chunks + hc) * p.hkv + kvh;
-    return p.part + (slot * 4 + wave) * (32 * D) + 4 * lane;
+    const float* const o = p.part + (slot * 4 + qw) * (32 * D) + 256 * KW * wave_id() + 4 * lane;
+#pragma unroll
+    for (int k = 0; k < KW; ++k) x[k] = *reinterpret_cast<const f32x4*>(o + 256 * k);
   };
-  f32x4 acc[4 * DB];
+  f32x4 acc[KW], x[4][KW];
+  auto add = [&](const f32x4 (&y)[KW]) {
 #pragma unroll
-  for (int k = 0; k < 4 * DB; ++k) acc[k] = *reinterpret_cast<const f32x4*>(at(0) + 256 * k);
-  int s = 1;
-  for (; s + 1 < n; s += 2) {
-    f32x4 x[4 * DB], y[4 * DB];
+    for (int k = 0; k < KW; ++k)
 #pragma unroll
-    for (int k = 0; k < 4 * DB; ++k) x[k] = *reinterpret_cast<const f32x4*>(at(s) + 256 * k);
+      for (int j = 0; j < 4; ++j) acc[k][j] += y[k][j];
+  };
+  read(acc, 0);
+  for (int s = 1; s < n; s += 4) {
 #pragma unroll
-    for (int k = 0; k < 4 * DB; ++k) y[k] = *reinterpret_cast<const f32x4*>(at(s + 1) + 256 * k);
+    for (int u = 0; u < 4; ++u) read(x[u], min(s + u, n - 1));
 #pragma unroll
-    for (int k = 0; k < 4 * DB; ++k)
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[k][j] = (acc[k][j] + x[k][j]) + y[k][j];
+    for (int u = 0; u < 4; ++u)
+      if (s + u < n) add(x[u]);
   }
-  if (s < n) {
-#pragma unroll
-    for (int k = 0; k < 4 * DB; ++k) {
-      const f32x4 x = *reinterpret_cast<const f32x4*>(at(s) + 256 * k);
-#pragma unroll
-      for (int j = 0; j < 4; ++j) acc[k][j] += x[j];
-    }
-  }
-  store_rows<D, RPW>(
-      smem, true,
-      [&](int db, int g) {
+  store_rows_shared<D, RPW>(
+      st,
+      [&](int k) {
         f32x4 v;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) v[j] = p.scale * acc[4 * db + g][j];
+        for (int j = 0; j < 4; ++j) v[j] = p.scale * acc[k][j];
         return v;
       },
-      q0 + wave * RPW, q1, p.hq, kvh * p.group + hc * HPW, p.dq, nullptr);
+      q0 + qw * RPW, q1, p.hq, kvh * p.group + hc * HPW, p.dq, nullptr);
 }
 
 template <int D>
 static hipError_t launch_dq_combine_d(const DqParams& p, int hpw, hipStream_t s) {
-  const dim3 grid(unsigned(p.n_comb) * p.hkv * p.head_chunks * 4), block(64);
+  const dim3 grid(unsigned(p.n_comb) * p.hkv * p.head_chunks * 4), block(256);
   switch (hpw) {
     case 1: hipLaunchKernelGGL((dq_combine_kernel<D, 1>), grid, block, 0, s, p); break;
     case 2: hipLaunchKernelGGL((dq_combine_kernel<D, 2>), grid, block, 0, s, p); break;

@@ -404,6 +404,54 @@ __device__ __forceinline__ void store_rows(char* region, bool active, Val val, i
   }
 }
 
+// The same for the combine passes, where the four waves of a workgroup share
+// one wave's 32 rows: wave w holds, for pair p = l % 32, the 16-byte pieces k =
+// w * D/32 + j in val(j) (piece k of lane l: columns 32 (k/4) + 8 (k%4) + 4
+// (l/32) + 0..3). `st`: 32 x D floats of shared memory. Contains a barrier.
+template <int D, int RPW, class Val>
+__device__ __forceinline__ void store_rows_shared(float* st, Val val, int row0, int row_end, int hq,
+                                                  int h0, float* out_f32, u16* out_bf16) {
+  constexpr int CH = D / 4, U = (32 / RPW) * D, KW = D / 32;
+  const int wave = wave_id(), lane = threadIdx.x & 63, p = lane & 31, half = lane >> 5;
+#pragma unroll
+  for (int j = 0; j < KW; ++j)
+    *reinterpret_cast<f32x4*>(st + p * D + 4 * ((2 * (wave * KW + j) + half) ^ (p % CH))) = val(j);
+  __syncthreads();
+  auto at = [&](int e, int& pr, int& row, size_t& gofs) {
+    const int r = e / U, u = e % U, hoff = u / D, dd = u % D;
+    pr = hoff * RPW + r;
+    row = row0 + r;
+    gofs = (size_t(row) * hq + h0 + hoff) * D + dd;
+    return dd;
+  };
+  if (out_f32) {
+#pragma unroll
+    for (int s = 0; s < D / 32; ++s) {
+      int pr, row;
+      size_t go;
+      const int dd = at(1024 * s + 4 * int(threadIdx.x), pr, row, go);
+      const f32x4 v = *reinterpret_cast<const f32x4*>(st + pr * D + 4 * ((dd / 4) ^ (pr % CH)));
+      if (row < row_end) *reinterpret_cast<f32x4*>(out_f32 + go) = v;
+    }
+  }
+  if (out_bf16) {
+#pragma unroll
+    for (int s = 0; s < D / 64; ++s) {
+      int pr, row;
+      size_t go;
+      const int dd = at(2048 * s + 8 * int(threadIdx.x), pr, row, go);
+      const f32x4 a = *reinterpret_cast<const f32x4*>(st + pr * D + 4 * ((dd / 4) ^ (pr % CH)));
+      const f32x4 b = *reinterpret_cast<const f32x4*>(st + pr * D + 4 * ((dd / 4 + 1) ^ (pr % CH)));
+      uint4 pk;
+      pk.x = uint32_t(f2bf(a[0])) | (uint32_t(f2bf(a[1])) << 16);
+      pk.y = uint32_t(f2bf(a[2])) | (uint32_t(f2bf(a[3])) << 16);
+      pk.z = uint32_t(f2bf(b[0])) | (uint32_t(f2bf(b[1])) << 16);
+      pk.w = uint32_t(f2bf(b[2])) | (uint32_t(f2bf(b[3])) << 16);
+      if (row < row_end) *reinterpret_cast<uint4*>(out_bf16 + go) = pk;
+    }
+  }
+}
+
 // Log-sum-exp merge of two partial results over disjoint key sets (weights
 // of the partials and the merged LSE, natural log; a -inf partial has
 // weight 0, so two empty partials merge to O = 0, LSE = -inf). One
