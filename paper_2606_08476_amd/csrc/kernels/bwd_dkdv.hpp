@@ -39,7 +39,7 @@ namespace fck {
 
 template <int D, bool DQ = false>
 struct DkdvLds {
-  // LSE/delta/limit slots, the key tile, two Q and two dO tiles; with DQ the
+  // -LSE/-delta/limit slots, the key tile, two Q and two dO tiles; with DQ the
   // transposed dS tile (128 keys x 32 queries, bf16) after them
   static constexpr uint32_t bytes = 6 * 256 + (128 + 4 * 32) * D * 2 + (DQ ? 128 * 32 * 2 : 0);
 };
@@ -56,8 +56,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
   constexpr int DB = D / 32;
   constexpr uint32_t KT = BN * D * 2;  // bytes of the key tile
   constexpr uint32_t QT = BM * D * 2;  // bytes of a Q or dO tile
-  // LDS layout (bytes): per buffer b, LSE at 256*3b, delta at +256, receive
-  // limits at +512 (a wave-wide copy each, the first BM entries used); then
+  // LDS layout (bytes): per buffer b, -LSE in log2 units at 256*3b, -delta at
+  // +256, receive limits at +512 (one wave each, the first BM entries used); then
   // the key tile; then Q and dO of buffer 0 and of buffer 1. The loop is
   // unrolled by two, so every read names its buffer with a compile-time
   // offset (all below 64 KiB, the reach of the offset field).
@@ -118,8 +118,15 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
     }
   };
 
-  // next iteration: Q/dO tiles, LSE, D and receive limits, all copied from
-  // HBM straight into LDS (rows past q1 repeat the last query; masked)
+  // next iteration: Q/dO tiles and receive limits, copied from HBM straight
+  // into LDS (rows past q1 repeat the last query; masked). LSE (wave 0) and D
+  // (wave 1) go through a register: put_rows stores them in the form the loop
+  // uses, once per iteration and row instead of once per score: 98 instead of
+  // 130 vector instructions beside an iteration's 32 MFMAs (backward of a 16K
+  // sequence, 32/8 heads: 1040 -> 1029 us; the same start of dP's accumulator in
+  // the dQ workgroups gave nothing: there -D is one register per lane, so
+  // setting 32 accumulators costs what the subtractions did).
+  float row_stat = 0.f;
   const TileLoader<D, BM, 256, RPI> ldq(p.hq * D, D);
   auto fetch = [&](int hh, int tt, int buf) {
     const int h = kvh * p.group + hh * HPI;
@@ -132,12 +139,17 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
     const uint32_t roff = 4u * uint32_t(min(t0 + m % RPI, q1 - 1));
     const uint32_t qoff = roff + 4u * uint32_t(m / RPI) * uint32_t(p.t_q);
     const uint32_t sm = sb + 768u * buf;
-    if (wave == 0)
-      lds_copy4(p.lse + (size_t)h * p.t_q, qoff, sm);
-    else if (wave == 1)
-      lds_copy4(p.delta + (size_t)h * p.t_q, qoff, sm + 256);
-    else if (wave == 2 && src)
+    if (wave < 2) {
+      const float* const rows = (wave == 0 ? p.lse : p.delta) + (size_t)h * p.t_q;
+      row_stat = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(rows) + qoff);
+    } else if (wave == 2 && src) {
       lds_copy4(p.lim, roff, sm + 512);
+    }
+  };
+  auto put_rows = [&](int buf) {
+    if (wave < 2)
+      *reinterpret_cast<float*>(smem + 768 * buf + 256 * wave + 4 * opaque(uint32_t(lane))) =
+          wave == 0 ? -row_stat * kLog2e : -row_stat;
   };
 
   // per-lane LDS byte offsets (swizzled tiles): row reads of a 32-row block
@@ -164,16 +176,20 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
     for (int ks = 0; ks < KS; ++ks) vreg[ks] = lds_b128(smem, 2u * uint32_t(vb ^ (ks << 4)), OQ0);
   }
   __syncthreads();  // every wave holds its V rows before the Q/dO copies
-  if (n_it > 0) fetch(0, 0, 0);
+  if (n_it > 0) {
+    fetch(0, 0, 0);
+    put_rows(0);
+  }
   advance();
   wait_async();
   __syncthreads();
 
   // One query tile. The 4*KS... MFMAs of the step run as one software
   // pipeline of slots, in this order:
-  //   S = Q K^T (KS slots); dP = dO V^T (KS slots, each also computing part of
-  //   P = exp(S - LSE)); dV += P^T dO (2*DB slots, each also computing part
-  //   of dS = P (dP - D)); dK += dS^T Q (2*DB slots).
+  //   S = Q K^T (KS slots); dP - D = dO V^T - D (KS slots, the accumulator
+  //   starting from -D; each also computing part of P = exp(S - LSE)); dV += P^T
+  //   dO (2*DB slots, each also computing part of dS = P (dP - D)); dK += dS^T Q
+  //   (2*DB slots).
   // Each slot issues the LDS reads of the slot two ahead, its MFMA, and its
   // share of the vector work, which then runs while the MFMA does; a
   // scheduling barrier after each slot keeps this order.
@@ -213,7 +229,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
     const int lo = !kval ? 0x40000000 : (diag && !src) ? kid - t0 - 4 * hf : -0x40000000;
     const int kl = (diag && src) ? (kval ? kid : 0x7fffffff) : -0x7fffffff;
 
-    f32x16 sacc = zero16(), dpacc = zero16();
+    f32x16 sacc = zero16(), dpacc;
     bf16x8 ra[3], rb[3], pa[2], sa[2];
     // Where P is large (short documents, keys near the diagonal) the bf16
     // rounding of P and dS dominates the dV/dK error. On a wave's tile with
@@ -235,7 +251,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
         __builtin_amdgcn_sched_barrier(0);
       });
     };
-    f32x4 l4[4], d4[4];
+    f32x4 l4[4];
     // P = 0 where the key is not seen: keys past the range, later keys on a
     // local diagonal, keys at or past a row's receive limit on a received
     // diagonal (edge tiles only)
@@ -276,14 +292,17 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
     static_for<0, NS>([&](auto nc) {
       constexpr int n = decltype(nc)::value;
       if (n + 2 < NS) rd(n + 2);
-      // LSE and delta of rows 8g + 4*half + 0..3, read two slots before the
+      // -LSE and -delta of rows 8g + 4*half + 0..3, read two slots before the
       // first slot that uses them
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
         if (KS + 4 * g / EP == n + 2)
           l4[g] = *reinterpret_cast<const f32x4*>(smem + SO + 4 * (8 * g + 4 * half));
-        if (2 * KS + 4 * g / ES == n + 2)
-          d4[g] = *reinterpret_cast<const f32x4*>(smem + SO + 256 + 4 * (8 * g + 4 * half));
+        if (KS == n + 2) {
+          const f32x4 d4 = *reinterpret_cast<const f32x4*>(smem + SO + 256 + 4 * (8 * g + 4 * half));
+#pragma unroll
+          for (int j = 0; j < 4; ++j) dpacc[4 * g + j] = d4[j];
+        }
       }
       const bf16x8& a = ra[n % 3];
       if (n < KS) {
@@ -293,7 +312,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
 #pragma unroll
         for (int e = (n - KS) * EP; e < (n - KS + 1) * EP; ++e) {
           const int g = e >> 2, j = e & 3;
-          sacc[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[e], sl2, -l4[g][j] * kLog2e));
+          sacc[e] = __builtin_amdgcn_exp2f(__builtin_fmaf(sacc[e], sl2, l4[g][j]));
         }
         if ((n - KS + 1) * EP == 8) pa[0] = pack8(sacc, 0);
         if (n == 2 * KS - 1) {
@@ -312,7 +331,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
         dv[db] = mfma32(pa[kh], a, dv[db]);
 #pragma unroll
         for (int e = u * ES; e < (u + 1) * ES; ++e)
-          dpacc[e] = sacc[e] * (dpacc[e] - d4[e >> 2][e & 3]);
+          dpacc[e] *= sacc[e];
         if ((u + 1) * ES == 8) sa[0] = pack8(dpacc, 0);
         if ((u + 1) * ES == 16) sa[1] = pack8(dpacc, 8);
         if (u == 2 * DB - 1 && split) {
@@ -430,6 +449,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
       if (!computed) put_ds(uint4{0u, 0u, 0u, 0u}, uint4{0u, 0u, 0u, 0u});
       dq_part(qacc);
     }
+    if (i_ + 1 < n_it) put_rows(decltype(bufc)::value ^ 1);
     wait_async();
     __syncthreads();
     if constexpr (DQ) dq_add(t0, hh, qacc);
