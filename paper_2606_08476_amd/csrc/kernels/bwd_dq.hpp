@@ -78,10 +78,10 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
   load_pairs<D, RPW>(lds_addr(smem), p.dout, q0, q1, p.hq, h0);
 
   bf16x8 qreg[KS], oreg[KS];
-  float lse2 = 0.f, del = 0.f;
+  float lse2 = 0.f, ndel = 0.f;
   if (qvalid) {
     lse2 = p.lse[(size_t)h * p.t_q + qrow] * kLog2e;
-    del = p.delta[(size_t)h * p.t_q + qrow];
+    ndel = -p.delta[(size_t)h * p.t_q + qrow];
   }
 
   // per-lane LDS byte offsets: K/V rows for k-step ks, and the two transpose
@@ -117,7 +117,7 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
   __syncthreads();
 
   // One key tile. Its MFMAs run as one software pipeline of slots:
-  //   S^T, keys 0-31; S^T, keys 32-63 (with P of keys 0-31); dP^T, keys 0-31
+  //   S^T, keys 0-31 (with the start of dP); S^T, keys 32-63 (with P of keys 0-31); dP^T, keys 0-31
   //   (with P of keys 32-63); dP^T, keys 32-63 (with dS of keys 0-31);
   //   dQ^T += K^T dS^T over keys 0-31 (with dS of keys 32-63), then 32-63.
   // Each slot issues the LDS reads of the slot two ahead, its MFMA and its
@@ -147,7 +147,7 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
       const int rel = (diag ? min(hi, qrow + 1) : hi) - k0 - 4 * half;
       const bool edge = diag || k0 + BN > hi;
 
-      f32x16 s[2] = {zero16(), zero16()}, dp[2] = {zero16(), zero16()};
+      f32x16 s[2] = {zero16(), zero16()}, dp[2];
       bf16x8 ring[3], sb[4];
       auto rd = [&](int n) {
         bf16x8& a = ring[n % 3];
@@ -170,7 +170,32 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
             s[mb][i] = 32 * mb + 8 * (i >> 2) + (i & 3) < rel ? s[mb][i] : 0.f;
         }
       };
-      auto dsv = [&](int mb, int i) { dp[mb][i] = s[mb][i] * (dp[mb][i] - del); };
+      // dP's accumulators start from -D, as in the dK/dV workgroups (whose dS
+      // has the same bits). At head dim 64 sixteen registers hold it for the
+      // first MFMA; at 128 there is no room for them, and the accumulators are
+      // set beside the first S products, which have no other vector work. Two
+      // registers per move, named here (the compiler would write two moves);
+      // volatile, so that they stay slots ahead of the MFMA that reads them.
+      // Layer of 16/8 heads of 64 over 32K tokens: 352 -> 344 us (120 instead
+      // of 152 vector instructions beside 24 MFMAs); at 128, within noise.
+      auto dp_init = [&](int mb) {
+        if constexpr (D == 64) {
+#pragma unroll
+          for (int i = 0; i < 16; ++i) dp[mb][i] = ndel;
+        } else {
+          typedef uint64_t u64x8 __attribute__((ext_vector_type(8)));
+          const uint32_t x = __builtin_bit_cast(uint32_t, ndel);
+          u64x8 y;
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            uint64_t r;
+            asm volatile("v_mov_b64 %0, %1" : "=v"(r) : "v"(uint64_t(x) << 32 | x));
+            y[i] = r;
+          }
+          dp[mb] = __builtin_bit_cast(f32x16, y);
+        }
+      };
+      auto dsv = [&](int mb, int i) { dp[mb][i] *= s[mb][i]; };
       rd(0);
       rd(1);
       static_for<0, NS>([&](auto nc) {
@@ -180,6 +205,7 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
         if (n < 2 * KS) {
           const int ks = n % KS, mb = n / KS;
           s[mb] = mfma32(a, qreg[ks], s[mb]);
+          if (mb == 0 && ks >= KS - 2) dp_init(ks - (KS - 2));
           if (mb == 1)
 #pragma unroll
             for (int e = ks * EP; e < (ks + 1) * EP; ++e) pexp(0, e);
