@@ -123,9 +123,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
   // (wave 1) go through a register: put_rows stores them in the form the loop
   // uses, once per iteration and row instead of once per score: 98 instead of
   // 130 vector instructions beside an iteration's 32 MFMAs (backward of a 16K
-  // sequence, 32/8 heads: 1040 -> 1029 us; the same start of dP's accumulator in
-  // the dQ workgroups gave nothing: there -D is one register per lane, so
-  // setting 32 accumulators costs what the subtractions did).
+  // sequence, 32/8 heads: 1040 -> 1029 us).
   float row_stat = 0.f;
   const TileLoader<D, BM, 256, RPI> ldq(p.hq * D, D);
   auto fetch = [&](int hh, int tt, int buf) {
@@ -241,13 +239,36 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
     // of a term.
     constexpr float kSplitP = 1.0f / 16.0f;
     bool split = false;
-    auto residual = [&](const bf16x8 (&lo)[2], uint32_t base, f32x16 (&acc)[DB]) {
-      static_for<0, 2 * DB>([&](auto uc) {
-        constexpr int u = decltype(uc)::value, kh = u / DB, db = u % DB;
+    // The branch is bound by its own latency: its 16 MFMAs' operands are read
+    // two ahead, as in the slots, the first before the residuals are formed;
+    // and the residuals take the bf16 values already packed (lo8). Layers with
+    // sharp attention (queries scaled by 3, 32/8 heads over 8K tokens), where
+    // it is common: 476 -> 467 us; headline 1671 -> 1669 us. Same bits.
+    auto residual = [&](const f32x16& pv, const bf16x8 (&pk)[2], const f32x16& sv,
+                        const bf16x8 (&sk)[2], bf16x8 (&ring)[3]) {
+      auto rd = [&](int n) {
+        const int u = n % (2 * DB), kh = u / DB, db = u % DB;
+        const uint32_t base = (n < 2 * DB ? OO : QO) + kh * 32 * D;
         const uint32_t t0_ = pt ^ (db << 6), t1_ = (pt ^ ((db << 6) | 32)) + 16 * D;
-        const bf16x8 b = cat8(lds_tr(smem, t0_, base + kh * 32 * D),
-                              lds_tr(smem, t1_, base + kh * 32 * D));
-        acc[db] = mfma32(lo[kh], b, acc[db]);
+        ring[n % 3] = cat8(lds_tr(smem, t0_, base), lds_tr(smem, t1_, base));
+      };
+      bf16x8 lo[2];
+      rd(0);
+      rd(1);
+      lo[0] = lo8(pv, 0, pk[0]);
+      lo[1] = lo8(pv, 8, pk[1]);
+      static_for<0, 4 * DB>([&](auto nc) {
+        constexpr int n = decltype(nc)::value, u = n % (2 * DB), kh = u / DB, db = u % DB;
+        if (n + 2 < 4 * DB) rd(n + 2);
+        if (n < 2 * DB)
+          dv[db] = mfma32(lo[kh], ring[n % 3], dv[db]);
+        else
+          dk[db] = mfma32(lo[kh], ring[n % 3], dk[db]);
+        // (P's residual of a half is last read by that half's last product)
+        if (n == 2 * DB - 1) {
+          lo[0] = lo8(sv, 0, sk[0]);
+          lo[1] = lo8(sv, 8, sk[1]);
+        }
         __builtin_amdgcn_sched_barrier(0);
       });
     };
@@ -334,15 +355,7 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
           dpacc[e] *= sacc[e];
         if ((u + 1) * ES == 8) sa[0] = pack8(dpacc, 0);
         if ((u + 1) * ES == 16) sa[1] = pack8(dpacc, 8);
-        if (u == 2 * DB - 1 && split) {
-          // (P and dS through opaque copies: the compiler would otherwise
-          // share their bf16 conversions with the packs above, converting
-          // element by element on the common path for this rare one)
-          f32x16 pf = sacc, sf = dpacc;
-          asm volatile("" : "+v"(pf), "+v"(sf));
-          residual({pack8_lo(pf, 0), pack8_lo(pf, 8)}, OO, dv);
-          residual({pack8_lo(sf, 0), pack8_lo(sf, 8)}, QO, dk);
-        }
+        if (u == 2 * DB - 1 && split) residual(sacc, pa, dpacc, sa, rb);
       } else {
         const int u = n - 2 * KS - 2 * DB, kh = u / DB, db = u % DB;
         dk[db] = mfma32(sa[kh], a, dk[db]);
