@@ -72,6 +72,11 @@ FwdWs fwd_ws(const View& v, int32_t mode) {
 // partial dQ of split query tiles
 size_t pass_ws(const View& v) { return v.part_bytes() + v.dq_part_bytes(); }
 size_t bwd_ws(const View& v) { return v.delta_bytes() + pass_ws(v); }
+// Whether the pass takes query tiles' key ranges in parts: only with a
+// workspace that holds their sums.
+bool split_dq(const View& v, const void* ws, size_t ws_bytes) {
+  return v.n_dq_slots && ws && ws_bytes >= pass_ws(v);
+}
 
 fck::FwdParams fwd_params(const View& v, const int32_t* items, int64_t n,
                           const void* q, const void* k_loc, const void* v_loc, const void* k_recv,
@@ -203,7 +208,7 @@ int run_pass(const View& v, const void* q, const void* k_loc, const void* v_loc,
                                 dk_loc, dv_loc, dk_recv, dv_recv, ws, v.part_bytes());
   if (deterministic) {
     fck::DqParams d = dq_params(v, q, k_loc, v_loc, k_recv, v_recv, lse, delta, dout, scale, dq);
-    if (v.n_dq_slots && ws_bytes >= pass_ws(v)) {
+    if (split_dq(v, ws, ws_bytes)) {
       d.items = v.dev_meta + v.off.dq_items;
       d.n_items = int32_t(v.dq_items.size() / 8);
       d.part = reinterpret_cast<float*>(static_cast<char*>(ws) + v.part_bytes());

@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -43,6 +44,8 @@ namespace {
 const char* g_blob = nullptr;   // the bound "device" blob
 size_t g_blob_bytes = 0;
 int64_t g_launches = 0;
+int g_split_views = 0;          // views with dQ parts and no split key tile
+bool g_dq_split = false;        // the last backward grid took dQ in parts
 
 void in_blob(const void* p, int64_t n_int32, const char* what) {
   if (n_int32 == 0) return;
@@ -96,6 +99,10 @@ hipError_t launch_bwd_atomic(const BwdParams& p, int, hipStream_t) {
 hipError_t launch_bwd_grid(const BwdParams& bp, const DqParams& dp, int, int, hipStream_t) {
   check_bwd(bp);
   in_blob(dp.items, 8 * int64_t(dp.n_items), "dQ items");
+  // parts of a key range have slots to go to, and are added up
+  in_blob(dp.comb, 8 * int64_t(dp.n_comb), "dQ combine entries");
+  CHECK((dp.n_comb > 0) == (dp.part != nullptr));
+  g_dq_split = dp.n_comb > 0;
   ++g_launches;
   return hipSuccess;
 }
@@ -241,6 +248,20 @@ void exercise_view(const std::vector<int32_t>& cu, const std::vector<fc_shard>& 
   CHECK(fc_attn_bwd_dkdv(v, D, D, D, D, D, Df, Df, D, 0.f, Df, Df, Df, Df, D, dws, nullptr) ==
         FC_OK);
   CHECK(fc_attn_bwd_dq(v, D, D, D, D, D, Df, Df, D, 0.f, Df, nullptr) == FC_OK);
+  // the pass splits query tiles' key ranges only with a workspace for the
+  // parts: a NULL one holds nothing, whatever its size is said to be
+  std::array<int32_t, 5> n_split{};
+  CHECK(fc_view_export_split(v, n_split.data(), nullptr, nullptr, nullptr, nullptr) == FC_OK);
+  if (i.t_q) {
+    auto pass = [&](void* ws, size_t bytes) {
+      return fc_attn_bwd_pass(v, D, D, D, D, D, Df, Df, D, 0.f, 1, Df, Df, Df, Df, Df, ws, bytes,
+                              nullptr);
+    };
+    CHECK(pass(D, dws) == FC_OK && g_dq_split == (n_split[2] > 0));
+    CHECK(pass(nullptr, size_t(1) << 40) == (i.n_bwd_slots ? FC_ERR_WORKSPACE : FC_OK));
+    CHECK(i.n_bwd_slots || !g_dq_split);
+    g_split_views += n_split[2] > 0 && !i.n_bwd_slots;
+  }
   if (i.t_q) {
     CHECK(fc_attn_bwd(v, nullptr, D, D, D, D, D, Df, Df, D, 0.f, 1, Df, Df, Df, Df, Df, D, bws,
                       nullptr) == FC_ERR_INVALID_ARG);
@@ -323,6 +344,17 @@ int main(int argc, char** argv) {
         }
     }
   }
+  // views whose long key ranges are split over workgroups
+  for (int len : {9000, 20000, 30000})
+    for (int cp : {2, 8})
+      for (int s = 0; s < 3; ++s) {
+        const int shapes[3][3] = {{4, 1, 128}, {8, 1, 128}, {16, 8, 64}};
+        const std::vector<int32_t> cu = {0, len, len + 1, len + 601};
+        const auto plan = plan_of(cu, cp, "per_doc");
+        exercise_view(cu, plan, cp, cp - 1, shapes[s][0], shapes[s][1], shapes[s][2], nullptr);
+        ++views;
+      }
+  CHECK(g_split_views > 0);
   // the workloads at full size
   if (argc > 1) {
     std::ifstream f(argv[1]);
