@@ -252,12 +252,18 @@ int fc_view_bind(fc_view view, void* dev_meta, size_t bytes, void* stream);
 void fc_view_destroy(fc_view view);
 
 /* Workspace bytes fc_attn_fwd (for `mode`), fc_attn_bwd and, alone,
- * fc_attn_bwd_dkdv / fc_attn_bwd_pass need (any pointer may be NULL). Two
- * calls also run with less, without splitting query tiles' key ranges (the
- * results then differ in their last bits): fc_attn_fwd with no workspace where
- * one pass suffices (FC_FUSED, or a view that receives nothing), and
- * fc_attn_bwd_dkdv / fc_attn_bwd_pass with a workspace that holds the partial
- * dK/dV of split key tiles alone. */
+ * fc_attn_bwd_dkdv / fc_attn_bwd_pass take (any pointer may be NULL). On a view
+ * whose long key ranges are split (fc_view_export_split) that includes the
+ * query tiles' partial results. With a workspace too small for those the calls
+ * below run the query tiles' ranges unsplit, and the results then differ in
+ * their last bits; they are refused (FC_ERR_WORKSPACE) only with less than that
+ * takes:
+ *   fc_attn_fwd                          FC_TWO_PASS on a view that receives keys:
+ *                                        the received partial O (128 rows x d
+ *                                        floats per workgroup); one pass: nothing
+ *   fc_attn_bwd_dkdv, fc_attn_bwd_pass   the partial dK/dV of split key tiles
+ * NULL holds nothing, whatever ws_bytes says. Calls whose work may overlap on
+ * the device need workspaces of their own. */
 int fc_workspace_size(fc_view view, int32_t mode, size_t* fwd_bytes, size_t* bwd_bytes,
                       size_t* dkdv_bytes);
 
@@ -282,7 +288,7 @@ int fc_kv_gather(fc_view view, const void* k_packed, const void* v_packed, int64
  * (fc_view_export_split) either mode runs the chunks as workgroups of their
  * own and merges them in a second launch, and the partial passes merge the
  * same chunks in the same order, so o and lse remain what the partial passes
- * and the merge write. ws: device, >= fc_workspace_size. */
+ * and the merge write. ws: device, >= fc_workspace_size; with less, as there. */
 int fc_attn_fwd(fc_view view, const void* q, const void* k_loc, const void* v_loc,
                 const void* k_recv, const void* v_recv, float scale, int32_t mode,
                 void* o, float* o_f32, float* lse, void* ws, size_t ws_bytes, void* stream);

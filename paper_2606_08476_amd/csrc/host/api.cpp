@@ -47,26 +47,22 @@ int hip_status(hipError_t e, const char* what) {
 
 float resolve_scale(float scale, int d) { return scale > 0.f ? scale : 1.f / std::sqrt(float(d)); }
 
-struct FwdWs {
-  size_t o_bytes, l_bytes, total;
-};
-// FC_TWO_PASS with received keys: the received partial's fp32 O (the
-// kernel merges it with the local partial in its epilogue), one slot of 32
-// rows x d per wave, four waves per workgroup of the launch
-// A split view, either mode: its chunks' partials.
-FwdWs fwd_ws(const View& v, int32_t mode) {
-  FwdWs w{};
-  if (v.fwd_chunk) {
-    w.total = align_up(v.fwd_split_bytes());
-    return w;
-  }
-  if (mode == FC_TWO_PASS && v.t_recv() > 0) {
-    const size_t wgs = (v.fwd_fused.size() / 8) * size_t(v.hkv) *
-                       size_t(v.hq / v.hkv / v.heads_per_tile);
-    w.o_bytes = align_up(wgs * 4 * 32 * size_t(v.d) * sizeof(float));
-    w.total = w.o_bytes;
-  }
-  return w;
+// Forward workspace of an unsplit run. FC_TWO_PASS with received keys: the
+// received partial's fp32 O (the kernel merges it with the local partial in
+// its epilogue), one slot of 32 rows x d per wave, four waves per workgroup of
+// the launch. One pass takes none.
+size_t whole_fwd_ws(const View& v, int32_t mode) {
+  if (mode != FC_TWO_PASS || v.t_recv() == 0) return 0;
+  return align_up((v.fwd_fused.size() / 8) * v.slot_bytes());
+}
+// The same, or the chunks' partials of a split view, in either mode.
+size_t fwd_ws(const View& v, int32_t mode) {
+  return v.fwd_chunk ? align_up(v.fwd_split_bytes()) : whole_fwd_ws(v, mode);
+}
+// Whether the forward takes key ranges in chunks: only with a workspace that
+// holds every chunk's partial.
+bool split_fwd(const View& v, int32_t mode, const void* ws, size_t ws_bytes) {
+  return v.fwd_chunk && ws && ws_bytes >= fwd_ws(v, mode);
 }
 // the backward pass's workspace: partial dK/dV of split key tiles, then
 // partial dQ of split query tiles
@@ -236,7 +232,7 @@ int fc_workspace_size(fc_view view, int32_t mode, size_t* fwd_bytes, size_t* bwd
   if (!view) return fail(FC_ERR_INVALID_ARG, "view is null");
   if (mode != FC_TWO_PASS && mode != FC_FUSED) return fail(FC_ERR_INVALID_ARG, "bad mode");
   const View& v = *reinterpret_cast<View*>(view);
-  if (fwd_bytes) *fwd_bytes = fwd_ws(v, mode).total;
+  if (fwd_bytes) *fwd_bytes = fwd_ws(v, mode);
   if (bwd_bytes) *bwd_bytes = bwd_ws(v);
   if (dkdv_bytes) *dkdv_bytes = pass_ws(v);
   return FC_OK;
@@ -336,16 +332,13 @@ int fc_attn_fwd(fc_view view, const void* q, const void* k_loc, const void* v_lo
   if (v->t_q() == 0) return FC_OK;
   if (!q || !k_loc || !v_loc || !o || !lse || (v->t_recv() && (!k_recv || !v_recv)))
     return fail(FC_ERR_INVALID_ARG, "null tensor pointer");
-  const FwdWs w = fwd_ws(*v, mode);
-  // (one pass needs no workspace: without one a split view takes it whole)
-  const bool one_pass = mode == FC_FUSED || v->t_recv() == 0;
-  const bool split = v->fwd_chunk && !(one_pass && (!ws || ws_bytes == 0));
-  if ((split || !one_pass) && (ws_bytes < w.total || (w.total && !ws)))
+  const size_t need = whole_fwd_ws(*v, mode);
+  if (need && (!ws || ws_bytes < need))
     return fail(FC_ERR_WORKSPACE, "forward workspace of " + std::to_string(ws_bytes) +
-                                      " bytes, need " + std::to_string(w.total));
+                                      " bytes, need " + std::to_string(need));
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const int32_t* m = v->dev_meta;
-  if (split) {
+  if (split_fwd(*v, mode, ws, ws_bytes)) {
     fck::FwdParams p = fwd_params(*v, nullptr, 0, q, k_loc, v_loc, k_recv, v_recv, scale);
     set_chunks(p, *v, ws);
     p.o_bf16 = static_cast<uint16_t*>(o);
@@ -353,7 +346,7 @@ int fc_attn_fwd(fc_view view, const void* q, const void* k_loc, const void* v_lo
     p.lse = lse;
     return hip_status(fck::launch_fwd(p, v->d, v->heads_per_tile, true, s), "attn_fwd launch");
   }
-  if (one_pass) {
+  if (mode == FC_FUSED || v->t_recv() == 0) {
     // one pass: both sources (fused items), or the local source alone
     const bool fused = mode == FC_FUSED && v->t_recv() > 0;
     fck::FwdParams p =

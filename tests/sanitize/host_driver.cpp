@@ -45,6 +45,7 @@ const char* g_blob = nullptr;   // the bound "device" blob
 size_t g_blob_bytes = 0;
 int64_t g_launches = 0;
 int g_split_views = 0;          // views with dQ parts and no split key tile
+bool g_fwd_split = false;       // the last forward was taken in chunks, in slots
 bool g_dq_split = false;        // the last backward grid took dQ in parts
 
 void in_blob(const void* p, int64_t n_int32, const char* what) {
@@ -70,6 +71,13 @@ hipError_t launch_fwd(const FwdParams& p, int d, int hpt, bool, hipStream_t) {
   CHECK((d == 64 || d == 128) && (hpt == 1 || hpt == 2 || hpt == 4) && p.n_items >= 0);
   CHECK(p.group % hpt == 0 && p.head_chunks * hpt == p.group && p.hq == p.group * p.hkv);
   in_blob(p.items, 8 * int64_t(p.n_items), "forward items");
+  in_blob(p.units, 8 * int64_t(p.n_units), "forward chunks");
+  in_blob(p.comb, 8 * int64_t(p.n_comb), "forward combine entries");
+  CHECK((p.n_units > 0) == (p.chunk > 0) && (p.n_comb > 0) == (p.chunk > 0));
+  // the final output is either taken whole or in chunks that have slots
+  CHECK(!p.o_bf16 || (p.chunk > 0) == (p.slots != nullptr));
+  CHECK((p.slots != nullptr) == (p.slot_lse != nullptr));
+  g_fwd_split = p.slots != nullptr;
   ++g_launches;
   return hipSuccess;
 }
@@ -201,6 +209,13 @@ void exercise_view(const std::vector<int32_t>& cu, const std::vector<fc_shard>& 
                               qf.data()) == FC_OK);
   CHECK(qcu[size_t(i.n_seg)] == i.t_q && rcu[size_t(i.n_seg)] == i.t_recv);
 
+  std::array<int32_t, 5> n_split{};
+  CHECK(fc_view_export_split(v, n_split.data(), nullptr, nullptr, nullptr, nullptr) == FC_OK);
+  // the received partials of an unsplit two-pass forward: four waves' 32 rows
+  // per workgroup of the launch
+  const size_t fwd_whole = (size_t(i.n_fwd_fused) * size_t(hkv) *
+                            size_t(hq / hkv / (128 / i.bm_fwd)) * 128 * size_t(d) * 4 + 255) /
+                           256 * 256;
   size_t fws = 0, bws = 0, dws = 0;
   CHECK(fc_workspace_size(v, FC_TWO_PASS, &fws, &bws, &dws) == FC_OK);
   // every device call on an unbound view is refused before any launch
@@ -225,10 +240,21 @@ void exercise_view(const std::vector<int32_t>& cu, const std::vector<fc_shard>& 
   for (int32_t mode : {FC_TWO_PASS, FC_FUSED}) {
     size_t need = 0;
     CHECK(fc_workspace_size(v, mode, &need, nullptr, nullptr) == FC_OK);
-    CHECK(fc_attn_fwd(v, D, D, D, D, D, 0.f, mode, D, Df, Df, D, need, nullptr) == FC_OK);
-    if (need && i.t_q)
-      CHECK(fc_attn_fwd(v, D, D, D, D, D, 0.f, mode, D, Df, Df, D, need - 1, nullptr) ==
-            FC_ERR_WORKSPACE);
+    auto fwd = [&](void* ws, size_t bytes) {
+      return fc_attn_fwd(v, D, D, D, D, D, 0.f, mode, D, Df, Df, ws, bytes, nullptr);
+    };
+    CHECK(fwd(D, need) == FC_OK && (!i.t_q || g_fwd_split == (n_split[0] > 0)));
+    if (i.t_q) {
+      // with less the forward runs unsplit, as long as what that takes is there:
+      // the received partials of two passes, nothing for one
+      const size_t whole = mode == FC_TWO_PASS && i.t_recv ? fwd_whole : 0;
+      CHECK(n_split[0] ? whole <= need : whole == need);
+      for (size_t bytes : {size_t(0), size_t(1), whole - 1, whole, need - 1})
+        if (bytes < need)
+          CHECK(fwd(D, bytes) == (bytes < whole ? FC_ERR_WORKSPACE : FC_OK) &&
+                (bytes < whole || !g_fwd_split));
+      CHECK(fwd(nullptr, need) == (whole ? FC_ERR_WORKSPACE : FC_OK) && (whole || !g_fwd_split));
+    }
   }
   CHECK(fc_attn_fwd(v, D, D, D, D, D, 0.f, 7, D, Df, Df, D, fws, nullptr) == FC_ERR_INVALID_ARG);
   CHECK(fc_attn_fwd_partial(v, 0, D, D, D, 0.f, Df, Df, nullptr) == FC_OK);
@@ -250,8 +276,6 @@ void exercise_view(const std::vector<int32_t>& cu, const std::vector<fc_shard>& 
   CHECK(fc_attn_bwd_dq(v, D, D, D, D, D, Df, Df, D, 0.f, Df, nullptr) == FC_OK);
   // the pass splits query tiles' key ranges only with a workspace for the
   // parts: a NULL one holds nothing, whatever its size is said to be
-  std::array<int32_t, 5> n_split{};
-  CHECK(fc_view_export_split(v, n_split.data(), nullptr, nullptr, nullptr, nullptr) == FC_OK);
   if (i.t_q) {
     auto pass = [&](void* ws, size_t bytes) {
       return fc_attn_bwd_pass(v, D, D, D, D, D, Df, Df, D, 0.f, 1, Df, Df, Df, Df, Df, ws, bytes,
