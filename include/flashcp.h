@@ -262,6 +262,8 @@ void fc_view_destroy(fc_view view);
  *                                        the received partial O (128 rows x d
  *                                        floats per workgroup); one pass: nothing
  *   fc_attn_bwd_dkdv, fc_attn_bwd_pass   the partial dK/dV of split key tiles
+ *   fc_attn_bwd                          the same and delta (Hq * T_q floats,
+ *                                        rounded up to 256 bytes)
  * NULL holds nothing, whatever ws_bytes says. Calls whose work may overlap on
  * the device need workspaces of their own. */
 int fc_workspace_size(fc_view view, int32_t mode, size_t* fwd_bytes, size_t* bwd_bytes,
@@ -288,7 +290,8 @@ int fc_kv_gather(fc_view view, const void* k_packed, const void* v_packed, int64
  * (fc_view_export_split) either mode runs the chunks as workgroups of their
  * own and merges them in a second launch, and the partial passes merge the
  * same chunks in the same order, so o and lse remain what the partial passes
- * and the merge write. ws: device, >= fc_workspace_size; with less, as there. */
+ * and the merge write. ws: device, >= fc_workspace_size, or
+ * less as told there. */
 int fc_attn_fwd(fc_view view, const void* q, const void* k_loc, const void* v_loc,
                 const void* k_recv, const void* v_recv, float scale, int32_t mode,
                 void* o, float* o_f32, float* lse, void* ws, size_t ws_bytes, void* stream);
@@ -328,7 +331,7 @@ int fc_lse_merge(const float* o_a, const float* lse_a, const float* o_b, const f
  * every dS of the row. Writes dq (fp32 [T_q,Hq,d],
  * 16-byte aligned), dk_loc/dv_loc (fp32 [T_q,Hkv,d]) and dk_recv/dv_recv
  * (fp32 [T_r,Hkv,d]); dK/dV are summed over the query heads of each KV
- * head. ws: device, >= bwd bytes of fc_workspace_size.
+ * head. ws: device, >= bwd bytes of fc_workspace_size, or less as told there.
  * deterministic != 0: no atomics anywhere, results bitwise reproducible for
  * fixed inputs (a query-major pass recomputes S and dP for dQ).
  * deterministic == 0: the key-major pass also adds dQ with fp32 atomics (no

@@ -488,7 +488,7 @@ int fc_attn_bwd(fc_view view, const void* q, const void* k_loc, const void* v_lo
   View* v;
   if (int rc = check_view(view, v)) return rc;
   if (v->t_q() == 0) return FC_OK;
-  const size_t need = bwd_ws(*v);
+  const size_t need = v->delta_bytes() + v->part_bytes();
   if (!ws || ws_bytes < need)
     return fail(FC_ERR_WORKSPACE, "backward workspace of " + std::to_string(ws_bytes) +
                                       " bytes, need " + std::to_string(need));

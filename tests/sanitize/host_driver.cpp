@@ -267,9 +267,17 @@ void exercise_view(const std::vector<int32_t>& cu, const std::vector<fc_shard>& 
                       nullptr) == FC_OK);
     CHECK(fc_attn_bwd_pass(v, D, D, D, D, D, Df, Df, D, 0.f, det, Df, Df, Df, Df, Df, D, dws,
                            nullptr) == FC_OK);
-    if (i.t_q)
-      CHECK(fc_attn_bwd(v, D, D, D, D, D, D, Df, Df, D, 0.f, det, Df, Df, Df, Df, Df, D, bws - 1,
-                        nullptr) == FC_ERR_WORKSPACE);
+    if (i.t_q) {
+      // delta and the split key tiles' partial dK/dV are enough: the query
+      // tiles' ranges then run whole
+      const size_t whole = bws - dws + 2 * size_t(i.n_bwd_slots) * size_t(hkv) * 128 * size_t(d) * 4;
+      for (size_t bytes : {bws, bws - 1, whole, whole - 1}) {
+        const int rc = fc_attn_bwd(v, D, D, D, D, D, D, Df, Df, D, 0.f, det, Df, Df, Df, Df, Df, D,
+                                   bytes, nullptr);
+        CHECK(rc == (bytes < whole ? FC_ERR_WORKSPACE : FC_OK));
+        if (rc == FC_OK && det) CHECK(g_dq_split == (bytes == bws && n_split[2] > 0));
+      }
+    }
   }
   CHECK(fc_attn_bwd_dkdv(v, D, D, D, D, D, Df, Df, D, 0.f, Df, Df, Df, Df, D, dws, nullptr) ==
         FC_OK);
