@@ -155,10 +155,11 @@ typedef struct {
   int32_t pad_;
   int64_t n_fwd_local, n_fwd_recv, n_fwd_fused, n_bwd; /* work items */
   int64_t pairs_loc, pairs_recv; /* visible (query, key) pairs per head */
-  int64_t meta_bytes;           /* device bytes fc_view_bind takes */
+  int64_t meta_bytes;           /* device bytes fc_view_bind takes ... */
   int64_t n_bwd_launch;         /* backward launch items after splitting long */
   int64_t n_bwd_reduce;         /*   key tiles; key tiles split; partial slots */
   int64_t n_bwd_slots;
+  int64_t table_bytes;          /* ... and the least it accepts: the tables alone */
 } fc_view_info;
 
 /* Tile shapes of a view; 0 in a field selects its default.
@@ -238,15 +239,16 @@ int fc_view_export_launch(fc_view view, int32_t* fwd_local, int32_t* fwd_recv,
 int fc_view_export_split(fc_view view, int32_t counts[5], int32_t* dq_items, int32_t* dq_comb,
                          int32_t* fwd_units, int32_t* fwd_comb);
 
-/* Upload the view's tables into `dev_meta` (device, >= meta_bytes, 256-byte
- * aligned) on `stream` and remember that buffer for later kernel calls. Where
- * the forward is split, meta_bytes covers the chunks' partial slots (the size
- * of fc_workspace_size) behind the tables: the partial passes, which take no
+/* Upload the view's tables into `dev_meta` (device, 256-byte aligned) on
+ * `stream` and remember that buffer for later kernel calls. Where the forward
+ * is split, meta_bytes covers the chunks' partial slots (the size of
+ * fc_workspace_size) behind the tables: the partial passes, which take no
  * workspace, write them. Calls on several streams or threads are ordered by
  * the library (the local and the received pass use slots of their own). A
- * buffer that holds the tables alone is accepted too: the partial passes then
- * run each query tile's chunks in one workgroup, as they do while a stream is
- * captured; the results are the same. */
+ * buffer of table_bytes or more, short of meta_bytes, holds the tables alone:
+ * the partial passes then run each query tile's chunks in one workgroup, as
+ * they do while a stream is captured; the results are the same. No other call
+ * uses those slots. */
 int fc_view_bind(fc_view view, void* dev_meta, size_t bytes, void* stream);
 
 void fc_view_destroy(fc_view view);

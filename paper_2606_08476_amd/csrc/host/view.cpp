@@ -594,6 +594,7 @@ int fc_view_get_info(fc_view view, fc_view_info* out) {
   out->n_bwd_launch = int64_t(v.bwd_launch.size() / 8);
   out->n_bwd_reduce = int64_t(v.bwd_reduce.size() / 8);
   out->n_bwd_slots = v.n_bwd_slots;
+  out->table_bytes = int64_t(v.table_bytes());
   return FC_OK;
 }
 

@@ -61,7 +61,7 @@ class ViewInfo(C.Structure):
         ("n_fwd_local", C.c_int64), ("n_fwd_recv", C.c_int64), ("n_fwd_fused", C.c_int64),
         ("n_bwd", C.c_int64), ("pairs_loc", C.c_int64), ("pairs_recv", C.c_int64),
         ("meta_bytes", C.c_int64), ("n_bwd_launch", C.c_int64), ("n_bwd_reduce", C.c_int64),
-        ("n_bwd_slots", C.c_int64),
+        ("n_bwd_slots", C.c_int64), ("table_bytes", C.c_int64),
     ]
 
     def as_dict(self):
@@ -284,16 +284,22 @@ class View:
                                                             for a in out.values()]))
         return dict(out, fwd_chunk=int(n[0]))
 
-    def bind(self, device="cuda", buf=None):
+    def bind(self, device="cuda", buf=None, slots=True):
         """Upload the view's tables on the current stream into ``buf`` (a
-        uint8 device tensor, allocated here if not given) and keep it."""
-        nbytes = self._info.meta_bytes
+        uint8 device tensor, allocated here if not given) and keep it.
+        ``slots``: with the slots that the partial passes of a split view use
+        (``meta_bytes``), as far as a given ``buf`` has room for them; without,
+        the tables alone (``table_bytes``)."""
+        need = self._info.table_bytes
+        nbytes = self._info.meta_bytes if slots else need
         if buf is None:
             _load_torch()
             buf = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
         off = (-buf.data_ptr()) % 256
-        if not buf.is_cuda or buf.numel() - off < nbytes:
+        if not buf.is_cuda or buf.numel() - off < need:
             raise ValueError("metadata buffer too small or not on the device")
+        if buf.numel() - off < nbytes:
+            nbytes = need
         self.meta = buf
         _check(lib().fc_view_bind(self.handle, buf.data_ptr() + off, nbytes, _stream()))
         return self

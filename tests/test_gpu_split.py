@@ -149,3 +149,29 @@ def test_split_views(key, dev):  # noqa: F811
         assert torch.equal(getattr(again, n), getattr(r, n)), n
     r.v.close()
     again.v.close()
+
+
+def _view(key):
+    kw = dict(CASES[key])
+    case = _cases.make_case(key, kw.pop("workload"), **kw)
+    return case, F.View(case.cu, case.plan, case.cp, case.rank, case.hq, case.hkv, case.d)
+
+
+def test_bind_buffers(dev):  # noqa: F811
+    """View.bind takes any buffer with room for the tables, with the slots
+    where they fit too, and allocates the tables alone on request; less than
+    the tables is refused."""
+    _, v = _view("local_g4")
+    i = v.info
+    tables, slots = i["table_bytes"], i["meta_bytes"] - i["table_bytes"]
+    assert slots > 0
+    size = lambda n: torch.empty(n, dtype=torch.uint8, device=dev)  # noqa: E731
+    big = size(i["meta_bytes"] + 512)
+    at = (-big.data_ptr()) % 256
+    for n in (tables, i["meta_bytes"] - 1, i["meta_bytes"]):
+        assert v.bind(dev, big[at:at + n]).meta.numel() == n
+    assert v.bind(dev).meta.numel() >= i["meta_bytes"]
+    assert v.bind(dev, slots=False).meta.numel() == tables + 256
+    with pytest.raises(ValueError):
+        v.bind(dev, big[at:at + tables - 1])
+    v.close()

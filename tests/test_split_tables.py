@@ -43,6 +43,7 @@ def check_split(v):
         assert sorted(by_slot) == list(range(len(u)))
         assert f_two == f_fused == -(-len(u) * (slot_bytes + slot_bytes // i["d"]) // 256) * 256
         assert i["meta_bytes"] > f_two   # the tables, then the same slots
+        assert i["table_bytes"] == i["meta_bytes"] - f_two
         seen = set()
         slots = []
         for q0, q1, first, n_r, n_l, *_ in comb.tolist():
@@ -64,7 +65,7 @@ def check_split(v):
         assert cost == sorted(cost, reverse=True)
     else:
         assert len(u) == len(comb) == 0
-        assert f_fused == 0
+        assert f_fused == 0 and i["table_bytes"] == i["meta_bytes"]
 
     # dQ parts
     d, comb = s["dq_items"], s["dq_comb"]
