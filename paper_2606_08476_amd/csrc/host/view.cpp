@@ -263,6 +263,7 @@ void View::build_dq_split() {
     const double bytes = double(slots) * slot_bytes();
     // what fits the static scratch of fc_attn_bwd_noalloc unsplit still does
     if (base <= FC_NOALLOC_SCRATCH_BYTES && base + bytes > FC_NOALLOC_SCRATCH_BYTES) continue;
+    if (bytes > double(slots_most())) continue;
     const double us = grid_us(double(parts), c) + combine_us(ceil_div(longest, c), bytes);
     if (us < best) {
       best = us;
@@ -341,6 +342,7 @@ void View::build_fwd_split() {
     if (launch_us(double(n), c) >= best) break;  // no chunk length helps less than this one
     int64_t units = 0;
     for (int32_t t : tiles) units += (t + c - 1) >> log2c;
+    if (double(units) * slot_bytes() * (1 + 1. / d) > double(slots_most())) continue;
     const double us = launch_us(double(units), c) +
                       combine_us(ceil_div(longest, c), double(units) * slot_bytes());
     if (us < best) {

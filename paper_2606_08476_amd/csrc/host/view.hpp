@@ -1,6 +1,7 @@
 // Host representation of a rank view (the opaque fc_view).
 #pragma once
 
+#include <algorithm>
 #include <cstdint>
 #include <vector>
 
@@ -78,6 +79,15 @@ struct View {
   }
   // one partial slot of a split query tile (forward or dQ): 128 rows x d
   size_t slot_bytes() const { return size_t(hkv) * head_chunks() * 128 * d * sizeof(float); }
+  // the most bytes the slots of either direction may take: a view keeps the
+  // forward's as long as it is bound, and a caller's workspaces hold both. Splits
+  // gain most on ranks with a small share of a long context, where ten times
+  // the output is common and small. By the estimated time, 256 MiB leave all but 1
+  // of 700 split views over 2K to 256K tokens their fastest split (3% slower);
+  // four times the output alone would slow half of them, by up to 3.9 times.
+  size_t slots_most() const {
+    return std::max(size_t(256) << 20, size_t(4) * t_q() * hq * d * sizeof(float));
+  }
   size_t dq_part_bytes() const { return size_t(n_dq_slots) * slot_bytes(); }
   // the split forward's slots, and behind them 128 LSEs per slot
   size_t fwd_slots_bytes() const { return fwd_units.size() / 8 * slot_bytes(); }

@@ -26,6 +26,12 @@ def _tiles(it):
             [(0, a, min(a + BN, l1)) for a in range(l0, l1, BN)])
 
 
+def _slots_most(i):
+    """The most bytes one direction's slots may take: 256 MiB, or four times the
+    rank's fp32 output if that is more."""
+    return max(256 << 20, 4 * 4 * i["t_q"] * i["hq"] * i["d"])
+
+
 def check_split(v):
     """Checks v's tables; returns (forward split, dQ split)."""
     i, e, s = v.info, v.export(), v.export_split()
@@ -44,6 +50,7 @@ def check_split(v):
         assert f_two == f_fused == -(-len(u) * (slot_bytes + slot_bytes // i["d"]) // 256) * 256
         assert i["meta_bytes"] > f_two   # the tables, then the same slots
         assert i["table_bytes"] == i["meta_bytes"] - f_two
+        assert f_two <= _slots_most(i) + 256
         seen = set()
         slots = []
         for q0, q1, first, n_r, n_l, *_ in comb.tolist():
@@ -70,6 +77,7 @@ def check_split(v):
     # dQ parts
     d, comb = s["dq_items"], s["dq_comb"]
     n_slots = int(sum(comb[:, 3]))
+    assert n_slots * slot_bytes <= _slots_most(i)
     part = 2 * i["n_bwd_slots"] * i["hkv"] * 128 * i["d"] * 4
     delta = -(-i["t_q"] * i["hq"] * 4 // 256) * 256
     assert dkdv == part + n_slots * slot_bytes and bwd == delta + dkdv
@@ -110,6 +118,18 @@ def test_split_tables_random():
             n += check_split(v)
             v.close()
     assert (n > 20).all(), n   # the rule does split, in both directions
+
+
+def test_slots_of_long_contexts_are_bounded():
+    """Long contexts over many ranks, whose best split by time would take more
+    than the bound (the first: 287 MiB for 30 MiB of output), or nearly."""
+    for lens, cp, (hq, hkv, d) in (([500000] + [10000] * 50, 32, (4, 4, 64)),
+                                   ([900000, 148576], 64, (4, 4, 64)),
+                                   ([300000, 212144], 64, (4, 1, 128))):
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        v = F.View(cu, F.fc_plan_per_doc(cu, cp), cp, cp - 1, hq, hkv, d)
+        check_split(v)
+        v.close()
 
 
 @pytest.mark.parametrize("name", list(synth.WORKLOADS))
