@@ -631,23 +631,12 @@ static hipError_t launch_partial_units_t(const FwdParams& p, hipStream_t s) {
     SlotGuard* const g = used[i];
     if (!g) continue;
     lock[i] = std::unique_lock<std::mutex>(g->mu);
-    if (g->event) {
-      if (const hipError_t e = hipStreamWaitEvent(s, static_cast<hipEvent_t>(g->event), 0);
-          e != hipSuccess)
-        return e;
-    } else {
-      hipEvent_t ev;
-      if (const hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming); e != hipSuccess)
-        return e;
-      g->destroy = [](void* x) { (void)hipEventDestroy(static_cast<hipEvent_t>(x)); };
-      g->event = ev;
-    }
+    if (const hipError_t e = g->wait(s); e != hipSuccess) return e;
   }
   if (const hipError_t e = launch_units_t<D, HPW>(p, s); e != hipSuccess) return e;
   for (SlotGuard* g : used)
     if (g)
-      if (const hipError_t e = hipEventRecord(static_cast<hipEvent_t>(g->event), s); e != hipSuccess)
-        return e;
+      if (const hipError_t e = g->used(s); e != hipSuccess) return e;
   return hipSuccess;
 }
 

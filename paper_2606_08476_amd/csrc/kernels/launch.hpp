@@ -10,16 +10,42 @@
 namespace fck {
 
 // Orders the uses of a view's own partial slots: every use waits, on its
-// stream, for the event the last use recorded there, so uses on several
-// streams or threads follow one another instead of racing. The event is made
-// by the first launch (which also says how to destroy it).
+// stream, for the event the last use on that stream's device recorded, so uses
+// on several streams or threads follow one another instead of racing. A view
+// bound again on another device has its slots there and starts an event of that
+// device's (an event is recorded on its own device only). Hold `mu` from wait()
+// to used().
 struct SlotGuard {
   std::mutex mu;
-  void* event = nullptr;
-  void (*destroy)(void*) = nullptr;
-  ~SlotGuard() {
-    if (event) destroy(event);
+
+  hipError_t wait(hipStream_t s) {
+    int cur = 0;
+    if (const hipError_t e = hipGetDevice(&cur); e != hipSuccess) return e;
+    dev_ = cur;
+    if (s)
+      if (const hipError_t e = hipStreamGetDevice(s, &dev_); e != hipSuccess) return e;
+    if (dev_ < 0 || dev_ >= kDevices) return hipErrorInvalidDevice;
+    hipEvent_t& ev = last_[dev_];
+    if (ev) return hipStreamWaitEvent(s, ev, 0);
+    if (dev_ != cur)
+      if (const hipError_t e = hipSetDevice(dev_); e != hipSuccess) return e;
+    const hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    if (e != hipSuccess) ev = nullptr;
+    if (dev_ != cur) (void)hipSetDevice(cur);
+    return e;
   }
+
+  hipError_t used(hipStream_t s) { return hipEventRecord(last_[dev_], s); }
+
+  ~SlotGuard() {
+    for (hipEvent_t ev : last_)
+      if (ev) (void)hipEventDestroy(ev);
+  }
+
+ private:
+  static constexpr int kDevices = 64;
+  hipEvent_t last_[kDevices] = {};  // by device, made by the first use there
+  int dev_ = 0;                     // the stream's device in wait()
 };
 
 struct FwdParams {

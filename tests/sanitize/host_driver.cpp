@@ -64,6 +64,50 @@ extern "C" hipError_t hipMemcpyAsync(void* dst, const void* src, size_t bytes, h
   std::memcpy(dst, src, bytes);
   return hipSuccess;
 }
+// Devices, streams and events for the slot guard: a stream's handle is 16 times
+// its device plus 1 (NULL: on the current device); an event remembers the device
+// that was current when it was made and can be recorded there only.
+namespace {
+struct StubEvent {
+  int device, records;
+};
+int g_device = 0;
+int g_events = 0;                    // alive
+const StubEvent* g_waited = nullptr;  // by the last hipStreamWaitEvent
+int device_of(hipStream_t s) { return s ? int(reinterpret_cast<uintptr_t>(s) / 16) : g_device; }
+}  // namespace
+extern "C" hipError_t hipGetDevice(int* d) {
+  *d = g_device;
+  return hipSuccess;
+}
+extern "C" hipError_t hipSetDevice(int d) {
+  g_device = d;
+  return hipSuccess;
+}
+extern "C" hipError_t hipStreamGetDevice(hipStream_t s, hipDevice_t* d) {
+  *d = device_of(s);
+  return hipSuccess;
+}
+extern "C" hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) {
+  *e = reinterpret_cast<hipEvent_t>(new StubEvent{g_device, 0});
+  ++g_events;
+  return hipSuccess;
+}
+extern "C" hipError_t hipEventDestroy(hipEvent_t e) {
+  delete reinterpret_cast<StubEvent*>(e);
+  --g_events;
+  return hipSuccess;
+}
+extern "C" hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+  StubEvent* const ev = reinterpret_cast<StubEvent*>(e);
+  if (ev->device != device_of(s)) return hipErrorInvalidHandle;
+  ++ev->records;
+  return hipSuccess;
+}
+extern "C" hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t e, unsigned) {
+  g_waited = reinterpret_cast<StubEvent*>(e);
+  return hipSuccess;
+}
 extern "C" const char* hipGetErrorString(hipError_t) { return "stub"; }
 
 namespace fck {
@@ -348,10 +392,37 @@ void error_paths() {
   fc_view_destroy(nullptr);
 }
 
+// Uses of a view's slots follow one another on each device the view is bound on
+// in turn, whichever device is current, and every event goes with the guard.
+void slot_guard() {
+  {
+    fck::SlotGuard g;
+    const StubEvent* last[2] = {nullptr, nullptr};
+    for (int use : {0, 0, 1, 1, 0, 1}) {
+      const hipStream_t s = reinterpret_cast<hipStream_t>(uintptr_t(16 * use + 1));
+      g_waited = nullptr;
+      CHECK(g.wait(s) == hipSuccess && g.used(s) == hipSuccess && g_device == 0);
+      // (a device's first use has nothing to wait for)
+      CHECK(g_waited == last[use]);
+      if (!last[use]) {
+        CHECK(g.wait(s) == hipSuccess);
+        last[use] = g_waited;
+      }
+      CHECK(last[use]->device == use && last[use]->records > 0);
+    }
+    g_device = 1;  // NULL: the current device's stream
+    CHECK(g.wait(nullptr) == hipSuccess && g_waited == last[1] && g.used(nullptr) == hipSuccess);
+    g_device = 0;
+    CHECK(g_events == 2);
+  }
+  CHECK(g_events == 0);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
   error_paths();
+  slot_guard();
   // random contexts: document counts, lengths (one-token documents
   // included), CP degrees, plans, every rank, several head shapes and tiles
   std::mt19937 rng(12345);
