@@ -68,62 +68,80 @@ class ViewInfo(C.Structure):
         return {k: getattr(self, k) for k, _ in self._fields_ if k != "pad_"}
 
 
-_lib = None
+_lib = _raw = None
 P = C.c_void_p
 I32P = C.POINTER(C.c_int32)
+
+
+def _signatures():
+    return {
+        "fc_plan_per_doc": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.POINTER(C.c_int64)],
+        "fc_plan_per_seq": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.POINTER(C.c_int64)],
+        "fc_plan_whole_lpt": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.POINTER(C.c_int64)],
+        "fc_plan_hybrid": [I32P, C.c_int32, C.c_int32, C.c_double, C.POINTER(Shard), C.c_int64,
+                           C.POINTER(C.c_int64), C.POINTER(C.c_uint8)],
+        "fc_plan_validate": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.c_int32],
+        "fc_plan_stats": [I32P, C.c_int32, C.c_int32, C.POINTER(Shard), C.c_int64, C.c_int32, C.c_int32,
+                          C.POINTER(C.c_int64), I32P, I32P, C.POINTER(C.c_int64), C.POINTER(C.c_int64),
+                          C.POINTER(C.c_double)],
+        "fc_view_create": [I32P, C.c_int32, C.POINTER(Shard), C.c_int64, C.c_int32, C.c_int32,
+                           C.c_int32, C.c_int32, C.c_int32, C.POINTER(TileCfg), C.POINTER(P)],
+        "fc_view_get_info": [P, C.POINTER(ViewInfo)],
+        "fc_view_export": [P] + [I32P] * 11,
+        "fc_view_bind": [P, P, C.c_size_t, P],
+        "fc_view_export_launch": [P] + [I32P] * 6,
+        "fc_view_export_split": [P] + [I32P] * 5,
+        "fc_workspace_size": [P, C.c_int32, C.POINTER(C.c_size_t), C.POINTER(C.c_size_t),
+                              C.POINTER(C.c_size_t)],
+        "fc_kv_gather": [P, P, P, C.c_int64, P, P, P, P, P],
+        "fc_attn_fwd": [P, P, P, P, P, P, C.c_float, C.c_int32, P, P, P, P, C.c_size_t, P],
+        "fc_attn_fwd_partial": [P, C.c_int32, P, P, P, C.c_float, P, P, P],
+        "fc_attn_fwd_partials": [P, P, P, P, P, P, C.c_float, P, P, P, P, P],
+        "fc_lse_merge": [P, P, P, P, C.c_int32, C.c_int32, C.c_int32, P, P, P, P],
+        "fc_attn_bwd": [P, P, P, P, P, P, P, P, P, P, C.c_float, C.c_int32, P, P, P, P, P, P,
+                        C.c_size_t, P],
+        "fc_bwd_preprocess": [P, P, P, P, P, P],
+        "fc_attn_bwd_pass": [P, P, P, P, P, P, P, P, P, C.c_float, C.c_int32, P, P, P, P, P, P,
+                             C.c_size_t, P],
+        "fc_attn_bwd_dkdv": [P, P, P, P, P, P, P, P, P, C.c_float, P, P, P, P, P, C.c_size_t, P],
+        "fc_attn_bwd_dq": [P, P, P, P, P, P, P, P, P, C.c_float, P, P],
+        "fc_attn_bwd_noalloc": [P, P, P, P, P, P, P, P, P, P, C.c_float, C.c_int32, P, P, P, P,
+                                P, P],
+    }
+
+
+def _open(raw):
+    """The native library; its pointer arguments typed as declared, or (raw)
+    plain addresses."""
+    if not os.path.exists(_LIB_PATH):
+        raise FileNotFoundError(f"{_LIB_PATH} is not built; run python -m paper_2606_08476_amd.build")
+    L = C.CDLL(_LIB_PATH)
+    for name, args in _signatures().items():
+        f = getattr(L, name)
+        f.argtypes = [P if raw and issubclass(a, C._Pointer) else a for a in args]
+        f.restype = C.c_int
+    L.fc_view_destroy.argtypes = [P]
+    L.fc_view_destroy.restype = None
+    L.fc_last_error.argtypes = []
+    L.fc_last_error.restype = C.c_char_p
+    return L
 
 
 def lib():
     """The loaded native library (loaded once)."""
     global _lib
     if _lib is None:
-        if not os.path.exists(_LIB_PATH):
-            raise FileNotFoundError(f"{_LIB_PATH} is not built; run python -m paper_2606_08476_amd.build")
-        L = C.CDLL(_LIB_PATH)
-        sig = {
-            "fc_plan_per_doc": [P, C.c_int32, C.c_int32, P, C.c_int64, P],
-            "fc_plan_per_seq": [P, C.c_int32, C.c_int32, P, C.c_int64, P],
-            "fc_plan_whole_lpt": [P, C.c_int32, C.c_int32, P, C.c_int64, P],
-            "fc_plan_hybrid": [P, C.c_int32, C.c_int32, C.c_double, P, C.c_int64,
-                               P, P],
-            "fc_plan_validate": [P, C.c_int32, C.c_int32, P, C.c_int64, C.c_int32],
-            "fc_plan_stats": [P, C.c_int32, C.c_int32, P, C.c_int64, C.c_int32, C.c_int32,
-                              P, P, P, P, P,
-                              P],
-            "fc_view_create": [P, C.c_int32, P, C.c_int64, C.c_int32, C.c_int32,
-                               C.c_int32, C.c_int32, C.c_int32, P, P],
-            "fc_view_get_info": [P, P],
-            "fc_view_export": [P] + [P] * 11,
-            "fc_view_bind": [P, P, C.c_size_t, P],
-            "fc_view_export_launch": [P] + [P] * 6,
-            "fc_view_export_split": [P] + [P] * 5,
-            "fc_workspace_size": [P, C.c_int32, P, P,
-                                  P],
-            "fc_kv_gather": [P, P, P, C.c_int64, P, P, P, P, P],
-            "fc_attn_fwd": [P, P, P, P, P, P, C.c_float, C.c_int32, P, P, P, P, C.c_size_t, P],
-            "fc_attn_fwd_partial": [P, C.c_int32, P, P, P, C.c_float, P, P, P],
-            "fc_attn_fwd_partials": [P, P, P, P, P, P, C.c_float, P, P, P, P, P],
-            "fc_lse_merge": [P, P, P, P, C.c_int32, C.c_int32, C.c_int32, P, P, P, P],
-            "fc_attn_bwd": [P, P, P, P, P, P, P, P, P, P, C.c_float, C.c_int32, P, P, P, P, P, P,
-                            C.c_size_t, P],
-            "fc_bwd_preprocess": [P, P, P, P, P, P],
-            "fc_attn_bwd_pass": [P, P, P, P, P, P, P, P, P, C.c_float, C.c_int32, P, P, P, P, P, P,
-                                 C.c_size_t, P],
-            "fc_attn_bwd_dkdv": [P, P, P, P, P, P, P, P, P, C.c_float, P, P, P, P, P, C.c_size_t, P],
-            "fc_attn_bwd_dq": [P, P, P, P, P, P, P, P, P, C.c_float, P, P],
-            "fc_attn_bwd_noalloc": [P, P, P, P, P, P, P, P, P, P, C.c_float, C.c_int32, P, P, P, P,
-                                    P, P],
-        }
-        for name, args in sig.items():
-            f = getattr(L, name)
-            f.argtypes = args
-            f.restype = C.c_int
-        L.fc_view_destroy.argtypes = [P]
-        L.fc_view_destroy.restype = None
-        L.fc_last_error.argtypes = []
-        L.fc_last_error.restype = C.c_char_p
-        _lib = L
+        _lib = _open(False)
     return _lib
+
+
+def _addr():
+    """The same for calls made with addresses of numpy arrays whose types are
+    set here (a typed pointer to one costs a microsecond or two)."""
+    global _raw
+    if _raw is None:
+        _raw = _open(True)
+    return _raw
 
 
 def _check(rc: int):
@@ -161,17 +179,17 @@ def _plan_out(fn, *args):
 
 def fc_plan_per_doc(cu, cp: int) -> np.ndarray:
     a, p, n = _cu(cu)
-    return _plan_out(lib().fc_plan_per_doc, p, n, cp)
+    return _plan_out(_addr().fc_plan_per_doc, p, n, cp)
 
 
 def fc_plan_per_seq(cu, cp: int) -> np.ndarray:
     a, p, n = _cu(cu)
-    return _plan_out(lib().fc_plan_per_seq, p, n, cp)
+    return _plan_out(_addr().fc_plan_per_seq, p, n, cp)
 
 
 def fc_plan_whole_lpt(cu, cp: int) -> np.ndarray:
     a, p, n = _cu(cu)
-    return _plan_out(lib().fc_plan_whole_lpt, p, n, cp)
+    return _plan_out(_addr().fc_plan_whole_lpt, p, n, cp)
 
 
 def fc_plan_hybrid(cu, cp: int, target_r: float = 1.05):
@@ -181,8 +199,8 @@ def fc_plan_hybrid(cu, cp: int, target_r: float = 1.05):
     cap = 4 * n + 4 * cp + 16
     while True:
         buf = np.empty((cap, 4), dtype=np.int32)
-        rc = lib().fc_plan_hybrid(p, n, cp, float(target_r), buf.ctypes.data, cap, C.byref(cnt),
-                                  isp.ctypes.data)
+        rc = _addr().fc_plan_hybrid(p, n, cp, float(target_r), buf.ctypes.data, cap, C.byref(cnt),
+                                    isp.ctypes.data)
         if rc == -7:
             cap = int(cnt.value)
             continue
@@ -193,7 +211,7 @@ def fc_plan_hybrid(cu, cp: int, target_r: float = 1.05):
 def fc_plan_validate(cu, cp: int, plan, require_equal_tokens: bool = False) -> None:
     a, p, n = _cu(cu)
     s, sp, m = _shards(plan)
-    _check(lib().fc_plan_validate(p, n, cp, sp, m, int(bool(require_equal_tokens))))
+    _check(_addr().fc_plan_validate(p, n, cp, sp, m, int(bool(require_equal_tokens))))
 
 
 def fc_plan_stats(cu, cp: int, plan, hkv: int, d: int) -> dict:
@@ -202,8 +220,8 @@ def fc_plan_stats(cu, cp: int, plan, hkv: int, d: int) -> dict:
     work = np.zeros(cp, dtype=np.int64)
     tok, rcv = np.zeros(cp, dtype=np.int32), np.zeros(cp, dtype=np.int32)
     eq4, eq5, imb = C.c_int64(0), C.c_int64(0), C.c_double(0)
-    _check(lib().fc_plan_stats(p, n, cp, sp, m, hkv, d, work.ctypes.data, tok.ctypes.data,
-                               rcv.ctypes.data, C.byref(eq4), C.byref(eq5), C.byref(imb)))
+    _check(_addr().fc_plan_stats(p, n, cp, sp, m, hkv, d, work.ctypes.data, tok.ctypes.data,
+                                 rcv.ctypes.data, C.byref(eq4), C.byref(eq5), C.byref(imb)))
     return dict(work=work.tolist(), tokens=tok.tolist(), recv_tokens=rcv.tolist(), eq4=eq4.value,
                 eq5=eq5.value, imbalance=imb.value)
 
@@ -221,7 +239,7 @@ class View:
         s, sp, m = _shards(plan)
         h = P()
         t = C.byref(TileCfg(*[int(x) for x in tiles])) if tiles is not None else None
-        _check(lib().fc_view_create(p, n, sp, m, cp, rank, hq, hkv, d, t, C.byref(h)))
+        _check(_addr().fc_view_create(p, n, sp, m, cp, rank, hq, hkv, d, t, C.byref(h)))
         self._h = h
         self.meta = None
         info = ViewInfo()

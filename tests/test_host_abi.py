@@ -296,3 +296,21 @@ def test_backward_workspace_holds_the_partial_slots():
         if name == "wholedoc":
             assert slots > 0
         v.close()
+
+
+def test_loaded_library_checks_pointer_types():
+    """lib() refuses pointers to other types than the declared ones, whatever the
+    binding itself passes."""
+    lib = F.lib()
+    cu = _cu([5, 3])
+    ok = (cu.ctypes.data_as(F.I32P), 2, 2)
+    buf, n = (F.Shard * 8)(), C.c_int64(0)
+    assert lib.fc_plan_per_doc(*ok, buf, 8, C.byref(n)) == 0
+    wide = cu.astype(np.int64)
+    for args in ((wide.ctypes.data_as(C.POINTER(C.c_int64)), 2, 2, buf, 8, C.byref(n)),
+                 (*ok, (C.c_int32 * 32)(), 8, C.byref(n)),
+                 (*ok, buf, 8, C.byref(C.c_int32(0))), (cu.ctypes.data, 2, 2, buf, 8, C.byref(n))):
+        with pytest.raises(C.ArgumentError):
+            lib.fc_plan_per_doc(*args)
+    with pytest.raises(C.ArgumentError):
+        lib.fc_workspace_size(None, 0, C.byref(C.c_int32(0)), None, None)
