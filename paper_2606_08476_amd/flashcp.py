@@ -149,17 +149,26 @@ def _check(rc: int):
         raise FlashCPError(rc, lib().fc_last_error().decode())
 
 
+def _i32(x):
+    """x as a contiguous, aligned int32 array (keep it alive during the call) and
+    its address."""
+    a = np.ascontiguousarray(np.asarray(x, dtype=np.int32))
+    if not a.flags.aligned:
+        a = a.copy()
+    return a, a.ctypes.data
+
+
 def _cu(cu):
-    a = np.ascontiguousarray(np.asarray(cu, dtype=np.int32))
-    return a, a.ctypes.data, int(a.size - 1)
+    a, p = _i32(cu)
+    return a, p, int(a.size - 1)
 
 
 def _shards(plan):
-    """The plan as an int32 [n, 4] array (the layout of fc_shard; keep it alive
-    during the call), its address and n. (Addresses of numpy arrays
-    throughout: an array type made per call, Shard * n, costs some 50 us.)"""
-    plan = np.ascontiguousarray(np.asarray(plan, dtype=np.int32).reshape(-1, 4))
-    return plan, plan.ctypes.data, len(plan)
+    """The plan as an int32 [n, 4] array (the layout of fc_shard), its address and
+    n. (Addresses of numpy arrays throughout: an array type made per call, Shard *
+    n, costs some 50 us.)"""
+    a, p = _i32(np.asarray(plan, dtype=np.int32).reshape(-1, 4))
+    return a, p, len(a)
 
 
 def _plan_out(fn, *args):

@@ -314,3 +314,20 @@ def test_loaded_library_checks_pointer_types():
             lib.fc_plan_per_doc(*args)
     with pytest.raises(C.ArgumentError):
         lib.fc_workspace_size(None, 0, C.byref(C.c_int32(0)), None, None)
+
+
+def test_plans_at_any_address():
+    """A plan or lengths at an address that is no multiple of 4 reach the library
+    at one that is."""
+    cu = _cu([50, 30, 20])
+    plan = F.fc_plan_per_doc(cu, 2)
+
+    def odd(a):
+        raw = np.zeros(a.nbytes + 1, dtype=np.uint8)
+        raw[1:] = np.frombuffer(a.tobytes(), dtype=np.uint8)
+        return raw[1:].view(np.int32).reshape(a.shape)
+
+    assert not odd(plan).flags.aligned
+    assert F._shards(odd(plan))[1] % 4 == 0 and F._cu(odd(cu))[1] % 4 == 0
+    F.fc_plan_validate(odd(cu), 2, odd(plan))
+    assert np.array_equal(F.fc_plan_per_doc(odd(cu), 2), plan)
