@@ -117,7 +117,7 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
   __syncthreads();
 
   // One key tile. Its MFMAs run as one software pipeline of slots:
-  //   S^T, keys 0-31 (with the start of dP); S^T, keys 32-63 (with P of keys 0-31); dP^T, keys 0-31
+  //   S^T, keys 0-31; S^T, keys 32-63 (with P of keys 0-31); dP^T, keys 0-31
   //   (with P of keys 32-63); dP^T, keys 32-63 (with dS of keys 0-31);
   //   dQ^T += K^T dS^T over keys 0-31 (with dS of keys 32-63), then 32-63.
   // Each slot issues the LDS reads of the slot two ahead, its MFMA and its
@@ -125,6 +125,7 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
   // barrier after each slot keeps this order.
   constexpr int NS = 4 * KS + 4 * DB;        // slots per tile
   constexpr int EP = 16 / KS, EQ = 8 / DB;   // elements per slot (P, dS)
+  constexpr int INIT0 = KS - 2, INIT1 = D == 64 ? KS - 1 : 3 * KS - 2;  // of dP, see below
   auto step = [&](int j, auto buf) {
     constexpr uint32_t KO = decltype(buf)::value * 2 * TILE, VO = KO + TILE;
     if (j + 1 < n_t) fetch(j + 1, 2 * TILE - KO);
@@ -173,11 +174,14 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
       // dP's accumulators start from -D, as in the dK/dV workgroups (whose dS
       // has the same bits). At head dim 64 sixteen registers hold it for the
       // first MFMA; at 128 there is no room for them, and the accumulators are
-      // set beside the first S products, which have no other vector work. Two
-      // registers per move, named here (the compiler would write two moves);
-      // volatile, so that they stay slots ahead of the MFMA that reads them.
-      // Layer of 16/8 heads of 64 over 32K tokens: 352 -> 344 us (120 instead
-      // of 152 vector instructions beside 24 MFMAs); at 128, within noise.
+      // set: the first 32 keys' beside the first S products, which have no other
+      // vector work, the others' two slots before they are read (set together
+      // with the first, sixteen registers live through eight more slots cost the
+      // grid a spill; either is as fast). Two registers per move, named here
+      // (the compiler would write two moves); volatile, so that they stay slots
+      // ahead of the MFMA that reads them. Layer of 16/8 heads of 64 over 32K
+      // tokens: 349 -> 342 us (120 instead of 152 vector instructions beside 24
+      // MFMAs); at 128, within noise.
       auto dp_init = [&](int mb) {
         if constexpr (D == 64) {
 #pragma unroll
@@ -205,13 +209,15 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
         if (n < 2 * KS) {
           const int ks = n % KS, mb = n / KS;
           s[mb] = mfma32(a, qreg[ks], s[mb]);
-          if (mb == 0 && ks >= KS - 2) dp_init(ks - (KS - 2));
+          if (n == INIT0) dp_init(0);
+          if (n == INIT1) dp_init(1);
           if (mb == 1)
 #pragma unroll
             for (int e = ks * EP; e < (ks + 1) * EP; ++e) pexp(0, e);
         } else if (n < 4 * KS) {
           const int ks = n % KS, mb = (n - 2 * KS) / KS;
           dp[mb] = mfma32(a, oreg[ks], dp[mb]);
+          if (n == INIT1) dp_init(1);
           if (mb == 1 && ks == 0) mask(0);
           if (mb == 0) {
 #pragma unroll
