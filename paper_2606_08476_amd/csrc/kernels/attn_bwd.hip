@@ -14,15 +14,19 @@ static int heads_per_iteration(int group) { return group % 4 == 0 ? 4 : group % 
 template <int D, int HPI>
 __global__ __launch_bounds__(256, 2) void attn_bwd_kernel(BwdParams p) {
   __shared__ __attribute__((aligned(16))) char smem[DkdvLds<D>::bytes];
-  dkdv_tile<D, false, HPI>(p, blockIdx.x, smem);
+  dkdv_tile<D, false, HPI, kKeepAll>(p, blockIdx.x, smem);
 }
 
 // The non-deterministic backward pass: key tiles only, each also adding its
 // share of dQ into p.dq (zeroed beforehand) with atomics.
+// (kKeepNone: all the registers are taken. Kept values spilled 4 at head dim 128
+// and two heads per iteration, 16/8 heads over 32K tokens 1114 -> 1107 us; at 64
+// their lack leaves three waves per SIMD, 16/8 heads over 16K tokens with queries
+// scaled by 3, 462 -> 443 us.)
 template <int D, int HPI>
 __global__ __launch_bounds__(256, 2) void attn_bwd_atomic_kernel(BwdParams p) {
   __shared__ __attribute__((aligned(16))) char smem[DkdvLds<D, true>::bytes];
-  dkdv_tile<D, true, HPI>(p, blockIdx.x, smem);
+  dkdv_tile<D, true, HPI, kKeepNone>(p, blockIdx.x, smem);
 }
 
 // The whole backward pass in one launch: the first n_dkdv workgroups take
@@ -34,7 +38,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_grid_kernel(BwdParams bp, DqP
   __shared__ __attribute__((aligned(16))) char smem[kBytes];
   const int b = blockIdx.x;
   if (b < n_dkdv)
-    dkdv_tile<D, false, HPI>(bp, b, smem);
+    dkdv_tile<D, false, HPI, kKeepAll>(bp, b, smem);
   else
     dq_tile<D, HPW>(dp, b - n_dkdv, smem);
 }

@@ -44,9 +44,12 @@ struct DkdvLds {
   static constexpr uint32_t bytes = 6 * 256 + (128 + 4 * 32) * D * 2 + (DQ ? 128 * 32 * 2 : 0);
 };
 
+// What the residual branch has kept of the bf16 roundings it subtracts.
+enum { kKeepNone = 0, kKeepAll = 1 };
+
 // One workgroup's key tile (workgroup index b); smem: DkdvLds<D, DQ>::bytes
 // of shared memory. HPI (1, 2 or 4) must divide the group size.
-template <int D, bool DQ = false, int HPI = 1>
+template <int D, bool DQ, int HPI, int KEEP>
 __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem) {
   constexpr int BN = 128;       // keys per workgroup
   constexpr int BM = 32;        // (query row, head) pairs per iteration
@@ -241,9 +244,11 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
     bool split = false;
     // The branch is bound by its own latency: its 16 MFMAs' operands are read
     // two ahead, as in the slots, the first before the residuals are formed;
-    // and the residuals take the bf16 values already packed (lo8). Layers with
-    // sharp attention (queries scaled by 3, 32/8 heads over 8K tokens), where
-    // it is common: 476 -> 467 us; headline 1671 -> 1669 us. Same bits.
+    // and the residuals take the bf16 values already packed (lo8), where KEEP
+    // says that there are registers for them up to here; elsewhere the values
+    // are rounded once more from a copy of P and dS. Same bits. Layers with sharp
+    // attention (queries scaled by 3, 32/8 heads over 8K tokens), where the
+    // branch is common: backward 340 -> 325 us with the values kept, 331 without.
     auto residual = [&](const f32x16& pv, const bf16x8 (&pk)[2], const f32x16& sv,
                         const bf16x8 (&sk)[2], bf16x8 (&ring)[3]) {
       auto rd = [&](int n) {
@@ -252,11 +257,17 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
         const uint32_t t0_ = pt ^ (db << 6), t1_ = (pt ^ ((db << 6) | 32)) + 16 * D;
         ring[n % 3] = cat8(lds_tr(smem, t0_, base), lds_tr(smem, t1_, base));
       };
+      // (opaque copies: the compiler would otherwise share their roundings with
+      // the packs above, and convert element by element on the common path)
+      f32x16 pf = pv, sf = sv;
+      if constexpr (KEEP == kKeepNone) asm volatile("" : "+v"(pf), "+v"(sf));
+      auto p_lo = [&](int i) { return KEEP == kKeepNone ? lo8(pf, 8 * i) : lo8(pf, 8 * i, pk[i]); };
+      auto s_lo = [&](int i) { return KEEP == kKeepNone ? lo8(sf, 8 * i) : lo8(sf, 8 * i, sk[i]); };
       bf16x8 lo[2];
       rd(0);
       rd(1);
-      lo[0] = lo8(pv, 0, pk[0]);
-      lo[1] = lo8(pv, 8, pk[1]);
+      lo[0] = p_lo(0);
+      lo[1] = p_lo(1);
       static_for<0, 4 * DB>([&](auto nc) {
         constexpr int n = decltype(nc)::value, u = n % (2 * DB), kh = u / DB, db = u % DB;
         if (n + 2 < 4 * DB) rd(n + 2);
@@ -266,8 +277,8 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
           dk[db] = mfma32(lo[kh], ring[n % 3], dk[db]);
         // (P's residual of a half is last read by that half's last product)
         if (n == 2 * DB - 1) {
-          lo[0] = lo8(sv, 0, sk[0]);
-          lo[1] = lo8(sv, 8, sk[1]);
+          lo[0] = s_lo(0);
+          lo[1] = s_lo(1);
         }
         __builtin_amdgcn_sched_barrier(0);
       });

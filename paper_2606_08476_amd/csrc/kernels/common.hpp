@@ -112,9 +112,15 @@ __device__ __forceinline__ bf16x8 pack8(const f32x16& c, int i0) {
 // With pack8 it splits each value into a high and a low bf16 part whose sum
 // carries about 16 significant bits (a product taken over both parts is as
 // exact as its fp32 accumulation).
-// `hi` is the packed bf16 rounding; its values come from its bits, through an
-// opaque copy (the compiler would otherwise undo the packing on the path that
-// made it, and convert element by element there).
+__device__ __forceinline__ bf16x8 lo8(const f32x16& c, int i0) {
+  bf16x8 r;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) r[j] = (__bf16)(c[i0 + j] - (float)(__bf16)c[i0 + j]);
+  return r;
+}
+// The same with the rounding already packed in `hi`, whose values come from its
+// bits, through an opaque copy (the compiler would otherwise undo the packing
+// on the path that made it, and convert element by element there).
 __device__ __forceinline__ bf16x8 lo8(const f32x16& c, int i0, const bf16x8& hi) {
   typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
   u32x4 w = __builtin_bit_cast(u32x4, hi);
