@@ -11,10 +11,15 @@ namespace fck {
 // group.
 static int heads_per_iteration(int group) { return group % 4 == 0 ? 4 : group % 2 == 0 ? 2 : 1; }
 
+// (Three waves per SIMD at head dim 64, for which the residual branch gives up P's
+// packed values. With two and the values: 64/16 heads of 64 over 64K tokens 1757
+// us, 32/8 over 16K with queries scaled by 3, 216; now 1585 and 199. At 128 there
+// are two either way, and the values kept are worth 286 -> 279 us, 32/8 heads
+// over 8K tokens scaled by 3.)
 template <int D, int HPI>
-__global__ __launch_bounds__(256, 2) void attn_bwd_kernel(BwdParams p) {
+__global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bwd_kernel(BwdParams p) {
   __shared__ __attribute__((aligned(16))) char smem[DkdvLds<D>::bytes];
-  dkdv_tile<D, false, HPI, kKeepAll>(p, blockIdx.x, smem);
+  dkdv_tile<D, false, HPI, D == 64 ? kKeepDs : kKeepAll>(p, blockIdx.x, smem);
 }
 
 // The non-deterministic backward pass: key tiles only, each also adding its
@@ -40,7 +45,7 @@ __global__ __launch_bounds__(256, 2) void attn_bwd_grid_kernel(BwdParams bp, DqP
   if (b < n_dkdv)
     dkdv_tile<D, false, HPI, kKeepAll>(bp, b, smem);
   else
-    dq_tile<D, HPW>(dp, b - n_dkdv, smem);
+    dq_tile<D, HPW, D == 64>(dp, b - n_dkdv, smem);
 }
 
 // (HPW, the dQ workgroups' heads per tile, divides the group as HPI does,

@@ -4,10 +4,16 @@
 
 namespace fck {
 
+// Head dim 64: -D held in registers leaves two waves per SIMD, without it the
+// four-heads tile runs three. It gains on many workgroups (64/16 heads over 64K
+// tokens 1163 -> 1110 us, 32/8 over 32K 254 -> 247) and loses on few (32/8 over 16K
+// 110 -> 118; D subtracted per score, 122); the other tiles, at or over the
+// three-wave limit without it, are faster with -D held (8/8 heads over 32K 109
+// against 112 us, 16/8 95 against 97).
 template <int D, int HPW>
-__global__ __launch_bounds__(256, 2) void attn_bwd_dq_kernel(DqParams p) {
+__global__ __launch_bounds__(256, D == 64 && HPW == 4 ? 3 : 2) void attn_bwd_dq_kernel(DqParams p) {
   __shared__ __attribute__((aligned(16))) char smem[DqLds<D>::bytes];
-  dq_tile<D, HPW>(p, blockIdx.x, smem);
+  dq_tile<D, HPW, D == 64 && HPW != 4>(p, blockIdx.x, smem);
 }
 
 template <int D>

@@ -45,7 +45,7 @@ struct DkdvLds {
 };
 
 // What the residual branch has kept of the bf16 roundings it subtracts.
-enum { kKeepNone = 0, kKeepAll = 1 };
+enum { kKeepNone = 0, kKeepDs = 1, kKeepAll = 2 };
 
 // One workgroup's key tile (workgroup index b); smem: DkdvLds<D, DQ>::bytes
 // of shared memory. HPI (1, 2 or 4) must divide the group size.
@@ -245,10 +245,11 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
     // The branch is bound by its own latency: its 16 MFMAs' operands are read
     // two ahead, as in the slots, the first before the residuals are formed;
     // and the residuals take the bf16 values already packed (lo8), where KEEP
-    // says that there are registers for them up to here; elsewhere the values
-    // are rounded once more from a copy of P and dS. Same bits. Layers with sharp
-    // attention (queries scaled by 3, 32/8 heads over 8K tokens), where the
-    // branch is common: backward 340 -> 325 us with the values kept, 331 without.
+    // says that there are registers for them up to here (P's would be dead by
+    // now, dS's are not); elsewhere the values are rounded once more from a copy
+    // of P or dS. Same bits. Layers with sharp attention (queries scaled by 3, 32/8
+    // heads over 8K tokens), where the branch is common: backward 340 -> 325 us
+    // with the values kept, 331 without.
     auto residual = [&](const f32x16& pv, const bf16x8 (&pk)[2], const f32x16& sv,
                         const bf16x8 (&sk)[2], bf16x8 (&ring)[3]) {
       auto rd = [&](int n) {
@@ -260,9 +261,10 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
       // (opaque copies: the compiler would otherwise share their roundings with
       // the packs above, and convert element by element on the common path)
       f32x16 pf = pv, sf = sv;
-      if constexpr (KEEP == kKeepNone) asm volatile("" : "+v"(pf), "+v"(sf));
-      auto p_lo = [&](int i) { return KEEP == kKeepNone ? lo8(pf, 8 * i) : lo8(pf, 8 * i, pk[i]); };
-      auto s_lo = [&](int i) { return KEEP == kKeepNone ? lo8(sf, 8 * i) : lo8(sf, 8 * i, sk[i]); };
+      if constexpr (KEEP < kKeepAll) asm volatile("" : "+v"(pf));
+      if constexpr (KEEP < kKeepDs) asm volatile("" : "+v"(sf));
+      auto p_lo = [&](int i) { return KEEP < kKeepAll ? lo8(pf, 8 * i) : lo8(pf, 8 * i, pk[i]); };
+      auto s_lo = [&](int i) { return KEEP < kKeepDs ? lo8(sf, 8 * i) : lo8(sf, 8 * i, sk[i]); };
       bf16x8 lo[2];
       rd(0);
       rd(1);

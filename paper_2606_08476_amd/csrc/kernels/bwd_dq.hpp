@@ -28,8 +28,8 @@ struct DqLds {
 };
 
 // One workgroup's query tile (workgroup index b); smem: DqLds<D>::bytes of
-// shared memory.
-template <int D, int HPW>
+// shared memory. HOLD: sixteen registers hold -D for dP's accumulators.
+template <int D, int HPW, bool HOLD>
 __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
   constexpr int BN = 64;
   constexpr int RPW = 32 / HPW;  // query rows per wave and head
@@ -125,7 +125,7 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
   // barrier after each slot keeps this order.
   constexpr int NS = 4 * KS + 4 * DB;        // slots per tile
   constexpr int EP = 16 / KS, EQ = 8 / DB;   // elements per slot (P, dS)
-  constexpr int INIT0 = KS - 2, INIT1 = D == 64 ? KS - 1 : 3 * KS - 2;  // of dP, see below
+  constexpr int INIT0 = KS - 2, INIT1 = HOLD ? KS - 1 : 3 * KS - 2;  // of dP, see below
   auto step = [&](int j, auto buf) {
     constexpr uint32_t KO = decltype(buf)::value * 2 * TILE, VO = KO + TILE;
     if (j + 1 < n_t) fetch(j + 1, 2 * TILE - KO);
@@ -172,18 +172,18 @@ __device__ __forceinline__ void dq_tile(const DqParams& p, int b, char* smem) {
         }
       };
       // dP's accumulators start from -D, as in the dK/dV workgroups (whose dS
-      // has the same bits). At head dim 64 sixteen registers hold it for the
-      // first MFMA; at 128 there is no room for them, and the accumulators are
-      // set: the first 32 keys' beside the first S products, which have no other
-      // vector work, the others' two slots before they are read (set together
-      // with the first, sixteen registers live through eight more slots cost the
-      // grid a spill; either is as fast). Two registers per move, named here
-      // (the compiler would write two moves); volatile, so that they stay slots
-      // ahead of the MFMA that reads them. Layer of 16/8 heads of 64 over 32K
+      // has the same bits). With HOLD (head dim 64) sixteen registers hold it
+      // for the first MFMA; at 128 there is no room for them, and the
+      // accumulators are set: the first 32 keys' beside the first S products,
+      // which have no other vector work, the others' two slots before they are
+      // read (set together with the first, sixteen registers live through eight
+      // more slots cost the grid a spill; either is as fast). Two registers per
+      // move, named here (the compiler would write two moves); volatile, so that
+      // they stay slots ahead of the MFMA that reads them. Layer of 16/8 heads of 64 over 32K
       // tokens: 349 -> 342 us (120 instead of 152 vector instructions beside 24
       // MFMAs); at 128, within noise.
       auto dp_init = [&](int mb) {
-        if constexpr (D == 64) {
+        if constexpr (HOLD) {
 #pragma unroll
           for (int i = 0; i < 16; ++i) dp[mb][i] = ndel;
         } else {

@@ -46,3 +46,12 @@ def test_no_attention_kernel_spills(kernels):
            for n, k in kernels.items()
            if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert not bad, bad
+
+
+# <head dim, heads per iteration or tile>
+THREE_WAVES = [f"{k}<64, {h}>" for k in ("attn_bwd_kernel", "attn_bwd_atomic_kernel") for h in (1, 2, 4)]
+
+
+@pytest.mark.parametrize("name", THREE_WAVES + ["attn_bwd_dq_kernel<64, 4>"])
+def test_three_waves_per_simd(kernels, name):
+    assert kernels[name][".vgpr_count"] <= 168 and kernels[name][".agpr_count"] == 0
