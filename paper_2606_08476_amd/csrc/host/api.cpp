@@ -290,7 +290,7 @@ int fc_attn_fwd_partial(fc_view view, int32_t src, const void* q, const void* k_
                             int64_t(v->fwd_recv.size() / 8), q, nullptr, nullptr, k_src, v_src,
                             scale);
   if (p.n_items == 0) return FC_OK;
-  set_chunks(p, *v, v->dev_slots);
+  set_chunks(p, *v, v->partial_slots[src] ? v->dev_slots : nullptr);
   // (its units read both sources: the one not asked for is skipped)
   if (src == 1 && p.chunk) {
     p.o_f32_recv = o_part;

@@ -310,6 +310,7 @@ void View::build_dq_split() {
 // estimate has to fall by 15%.
 void View::build_fwd_split() {
   fwd_chunk = 0;
+  partial_slots[0] = partial_slots[1] = false;
   fwd_units.clear();
   fwd_comb.clear();
   const bool wide = d == 128;
@@ -329,21 +330,21 @@ void View::build_fwd_split() {
   }
   // a launch of more workgroups than fit ends, on average, some way into the
   // longest of the items it starts last
-  auto launch_us = [&](double units, double most) {
-    const double fair = wgs * (double(total) * f2 + units * wg) / kSlotsResident;
+  auto launch_us = [&](double units, double most, int64_t sum) {
+    const double fair = wgs * (double(sum) * f2 + units * wg) / kSlotsResident;
     const double tail = units * wgs > kSlotsResident ? 0.3 * most * f1 : 0;
     return std::max(fair + tail, most * f1 + wg);
   };
-  const double whole = launch_us(double(n), longest);
+  const double whole = launch_us(double(n), longest, total);
   double best = 0.85 * whole;
   int32_t chunk = 0;
   for (int32_t log2c = 3; 1 << log2c < longest; ++log2c) {
     const int32_t c = 1 << log2c;
-    if (launch_us(double(n), c) >= best) break;  // no chunk length helps less than this one
+    if (launch_us(double(n), c, total) >= best) break;  // no chunk length helps less than this one
     int64_t units = 0;
     for (int32_t t : tiles) units += (t + c - 1) >> log2c;
     if (double(units) * slot_bytes() * (1 + 1. / d) > double(slots_most())) continue;
-    const double us = launch_us(double(units), c) +
+    const double us = launch_us(double(units), c, total) +
                       combine_us(ceil_div(longest, c), double(units) * slot_bytes());
     if (us < best) {
       best = us;
@@ -352,6 +353,30 @@ void View::build_fwd_split() {
   }
   if (!chunk) return;
   fwd_chunk = chunk;
+  // One source's partial pass by itself: slots and a second launch only where
+  // they beat one workgroup per query tile merging its chunks as it goes (2 us a
+  // chunk, 1 at head dim 64), by the same estimate and 2 us for the guard's
+  // events. Over 22 split views of 2K to 256K tokens it picks the faster one but
+  // for 1.7 us at most: mostly the chunks' workgroups for received keys (33 ->
+  // 20 us, 736 -> 465) and one per tile for the few local ones (14 -> 8 us,
+  // 58 -> 38).
+  for (int src = 0; src < 2; ++src) {
+    int64_t sum = 0, units = 0, n_src = 0;
+    int32_t most = 0;
+    for (size_t i = 0; i < n; ++i) {
+      const int32_t t = tiles[2 * i + 1 - src];
+      sum += t;
+      units += ceil_div(t, chunk);
+      n_src += t > 0;
+      most = std::max(most, t);
+    }
+    const int32_t merges = ceil_div(most, chunk);
+    if (merges < 2) continue;
+    const double alone = launch_us(double(n_src), most, sum) + (wide ? 2.0 : 1.0) * (merges - 1);
+    const double slots = launch_us(double(units), chunk, sum) + 2.0 +
+                         combine_us(merges, double(units) * slot_bytes());
+    partial_slots[src] = slots < 0.85 * alone;
+  }
   const int32_t len = chunk * bn_fwd;
   std::vector<int32_t> items;
   std::vector<int64_t> cost;

@@ -44,6 +44,8 @@ struct View {
   // fused items q0, q1, first slot, received chunks, local chunks, 0, 0, 0
   // (its slots: the received chunks, then the local ones)
   int32_t fwd_chunk = 0;
+  // whether the local, the received partial pass by itself takes the slots
+  bool partial_slots[2] = {false, false};
   std::vector<int32_t> fwd_units, fwd_comb;
 
   // device blob: every table above that a kernel reads (the forward lists in

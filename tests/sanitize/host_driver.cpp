@@ -44,6 +44,7 @@ namespace {
 const char* g_blob = nullptr;   // the bound "device" blob
 size_t g_blob_bytes = 0;
 int64_t g_launches = 0;
+int g_slot_passes[2] = {0, 0};  // local, received partial passes in slots
 int g_split_views = 0;          // views with dQ parts and no split key tile
 bool g_fwd_split = false;       // the last forward was taken in chunks, in slots
 bool g_dq_split = false;        // the last backward grid took dQ in parts
@@ -301,8 +302,17 @@ void exercise_view(const std::vector<int32_t>& cu, const std::vector<fc_shard>& 
     }
   }
   CHECK(fc_attn_fwd(v, D, D, D, D, D, 0.f, 7, D, Df, Df, D, fws, nullptr) == FC_ERR_INVALID_ARG);
-  CHECK(fc_attn_fwd_partial(v, 0, D, D, D, 0.f, Df, Df, nullptr) == FC_OK);
-  CHECK(fc_attn_fwd_partial(v, 1, D, D, D, 0.f, Df, Df, nullptr) == FC_OK);
+  // a partial pass by itself takes slots only where there is something to merge
+  std::vector<int32_t> comb(8 * size_t(n_split[4]) + 1);
+  CHECK(fc_view_export_split(v, n_split.data(), nullptr, nullptr, nullptr, comb.data()) == FC_OK);
+  for (int src : {0, 1}) {
+    g_fwd_split = false;
+    CHECK(fc_attn_fwd_partial(v, src, D, D, D, 0.f, Df, Df, nullptr) == FC_OK);
+    int most = 0;
+    for (int32_t k = 0; k < n_split[4]; ++k) most = std::max(most, comb[8 * size_t(k) + 4 - src]);
+    CHECK(most > 1 || !g_fwd_split);
+    g_slot_passes[src] += g_fwd_split;
+  }
   CHECK(fc_attn_fwd_partials(v, D, D, D, D, D, 0.f, Df, Df, Df, Df, nullptr) == FC_OK);
   CHECK(fc_bwd_preprocess(v, D, nullptr, D, Df, nullptr) == FC_OK);
   CHECK(fc_bwd_preprocess(v, nullptr, Df, D, Df, nullptr) == FC_OK);
@@ -457,7 +467,7 @@ int main(int argc, char** argv) {
         exercise_view(cu, plan, cp, cp - 1, shapes[s][0], shapes[s][1], shapes[s][2], nullptr);
         ++views;
       }
-  CHECK(g_split_views > 0);
+  CHECK(g_split_views > 0 && g_slot_passes[0] > 0 && g_slot_passes[1] > 0);
   // the workloads at full size
   if (argc > 1) {
     std::ifstream f(argv[1]);
