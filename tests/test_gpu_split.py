@@ -3,8 +3,9 @@ document much longer than the rest): every entry point against the fp64 oracle
 and against the others.
 
 The cases have key ranges that are whole multiples of the chunk length, one key
-more, shorter than one chunk and empty, one-token documents, both head dims and
-1, 4 and 8 query heads per KV head; the partial passes run over the view's own
+more, shorter than one chunk and empty, one-token documents, both head dims with
+each number of heads per workgroup (1, 2 and 4; ragged ones so that a wave's
+rows end inside it); the partial passes run over the view's own
 slots and, bound without them or captured into a graph, in one workgroup per
 query tile. Tolerances are those of the unsplit paths (test_gpu_parity);
 where the same sums are taken in another order in fp32, 2e-5 of the largest
@@ -38,6 +39,12 @@ CASES = {
                            plan="per_doc"),
     "long_d64_g1": dict(workload="tiny", lens=[7001, 1, 1, 300], cp=2, rank=1, hq=4, hkv=4,
                         plan="per_doc"),
+    "ragged_d64_g2": dict(workload="tiny", lens=[9001, 1, 77, 300], cp=4, rank=3, hq=4, hkv=2,
+                          plan="per_doc"),
+    "ragged_g1": dict(workload="llama8b", lens=[6007, 1, 130, 300], cp=4, rank=3, hq=2, hkv=2,
+                      plan="per_doc"),
+    "ragged_g2": dict(workload="llama8b", lens=[6007, 1, 130, 300], cp=4, rank=3, hq=4, hkv=2,
+                      plan="per_doc"),
 }
 
 
@@ -174,4 +181,74 @@ def test_bind_buffers(dev):  # noqa: F811
     assert v.bind(dev, slots=False).meta.numel() == tables + 256
     with pytest.raises(ValueError):
         v.bind(dev, big[at:at + tables - 1])
+    v.close()
+
+
+@pytest.mark.parametrize("key", ["long_g8", "aligned_d64_g8", "ragged_g2"])
+def test_short_workspaces(key, dev):  # noqa: F811
+    """With a workspace that holds no slots every call runs the ranges whole: the
+    forward against the oracle and the same bits whatever the size, the backward
+    the dQ of fc_attn_bwd_dq and the dK/dV of the split run. NULL holds nothing."""
+    kw = dict(CASES[key])
+    case = _cases.make_case(key, kw.pop("workload"), **kw)
+    r = Run(case, dev)
+    i, v = r.v.info, r.v
+    tq, hq, d = i["t_q"], i["hq"], i["d"]
+    O, L = r.oracle_fwd()
+    nan = lambda *sh, dt=torch.float32: torch.full(sh, float("nan"), dtype=dt, device=dev)  # noqa: E731
+    ws = lambda n: torch.empty(n, dtype=torch.uint8, device=dev)  # noqa: E731
+    kv = (r.k_loc, r.v_loc, r.k_recv, r.v_recv)
+    whole = -(-i["n_fwd_fused"] * i["hkv"] * (hq // i["hkv"] // (128 // i["bm_fwd"])) * 128 * d * 4
+              // 256) * 256
+    for mode, sizes in ((F.FC_FUSED, (0, 1, v.workspace_size(F.FC_FUSED)[0] - 1)),
+                        (F.FC_TWO_PASS, (whole, v.workspace_size(F.FC_TWO_PASS)[0] - 1))):
+        first = None
+        for n in sizes:
+            out = nan(tq, hq, d, dt=torch.bfloat16), nan(tq, hq, d), nan(hq, tq)
+            F.fc_attn_fwd(v, r.q, *kv, 0.0, mode, *out, ws(n))
+            torch.cuda.synchronize()
+            assert max(_maxabs(out[0], O), _maxabs(out[1], O)) <= O_TOL
+            assert _lse_ok(out[2], L) <= LSE_TOL
+            first = first or out
+            assert all(torch.equal(a, b) for a, b in zip(out, first))
+    delta, alone = torch.empty_like(r.lse), nan(tq, hq, d)
+    F.fc_bwd_preprocess(v, None, r.do, delta, o_f32=r.o32)
+    F.fc_attn_bwd_dq(v, r.q, *kv, r.lse, delta, r.do, 0.0, alone)
+    part = 2 * i["n_bwd_slots"] * i["hkv"] * 128 * d * 4
+    base = -(-tq * hq * 4 // 256) * 256 + part
+    for n in (base, v.workspace_size()[1] - 1):
+        out = r.bwd_outputs()
+        F.fc_attn_bwd(v, r.q, *kv, r.o, r.lse, r.do, 0.0, *out, ws(n), o_f32=r.o32)
+        torch.cuda.synchronize()
+        assert torch.equal(out[0], alone)
+        assert all(torch.equal(a, b) for a, b in
+                   zip(out[1:], (r.dk_loc, r.dv_loc, r.dk_recv, r.dv_recv)))
+    v.close()
+
+
+def test_sources_on_two_streams(dev):  # noqa: F811
+    """The local and the received pass of one view, each on a stream of its own and
+    several times over, then the two swapped: the bits of the passes run one
+    after the other."""
+    kw = dict(CASES["long_g4"])
+    case = _cases.make_case("long_g4", kw.pop("workload"), **kw)
+    r = Run(case, dev)
+    i, v = r.v.info, r.v
+    tq, hq, d = i["t_q"], i["hq"], i["d"]
+    nan = lambda *sh: torch.full(sh, float("nan"), device=dev)  # noqa: E731
+    kv = ((r.k_loc, r.v_loc), (r.k_recv, r.v_recv))
+    ref = [(nan(tq, hq, d), nan(hq, tq)) for _ in range(2)]
+    for src in (0, 1):
+        F.fc_attn_fwd_partial(v, src, r.q, *kv[src], 0.0, *ref[src])
+    outs = [[(nan(tq, hq, d), nan(hq, tq)) for _ in range(2)] for _ in range(6)]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    torch.cuda.synchronize()
+    for k, pair in enumerate(outs):
+        for src in (0, 1):
+            with torch.cuda.stream(streams[src ^ (k >= 3)]):
+                F.fc_attn_fwd_partial(v, src, r.q, *kv[src], 0.0, *pair[src])
+    torch.cuda.synchronize()
+    for pair in outs:
+        for src in (0, 1):
+            assert all(torch.equal(a, b) for a, b in zip(pair[src], ref[src]))
     v.close()
