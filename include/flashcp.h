@@ -248,7 +248,8 @@ int fc_view_export_split(fc_view view, int32_t counts[5], int32_t* dq_items, int
  * buffer of table_bytes or more, short of meta_bytes, holds the tables alone:
  * the partial passes then run each query tile's chunks in one workgroup, as
  * they do while a stream is captured; the results are the same. No other call
- * uses those slots. */
+ * uses those slots. The buffer must stay until the work of the calls made with
+ * it has ended. */
 int fc_view_bind(fc_view view, void* dev_meta, size_t bytes, void* stream);
 
 void fc_view_destroy(fc_view view);

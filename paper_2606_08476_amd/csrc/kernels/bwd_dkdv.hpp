@@ -125,8 +125,9 @@ __device__ __forceinline__ void dkdv_tile(const BwdParams& p, int b, char* smem)
   // into LDS (rows past q1 repeat the last query; masked). LSE (wave 0) and D
   // (wave 1) go through a register: put_rows stores them in the form the loop
   // uses, once per iteration and row instead of once per score: 98 instead of
-  // 130 vector instructions beside an iteration's 32 MFMAs (backward of a 16K
-  // sequence, 32/8 heads: 1040 -> 1029 us).
+  // 130 vector instructions beside an iteration's 32 MFMAs. That is worth 1% at
+  // most (backward of a 16K sequence, 32/8 heads, 1014 -> 1003 us where two runs
+  // differ by 5): issue slots are not what is short.
   float row_stat = 0.f;
   const TileLoader<D, BM, 256, RPI> ldq(p.hq * D, D);
   auto fetch = [&](int hh, int tt, int buf) {
