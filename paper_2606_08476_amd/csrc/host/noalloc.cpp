@@ -10,9 +10,10 @@
 // that device current) and that address alone is handed to the kernels.
 //
 // What the workspace holds needs no clearing: the preprocess writes every
-// delta the pass reads, and every split key tile's part writes the rows of
-// its slot that the reduce reads. Calls on one GPU share the array, so
-// calls whose work overlaps on that GPU (other streams, other threads) race.
+// delta the pass reads, and every part of a split key tile or of a split query
+// tile's key range writes the rows of its slot that are summed up. Calls on
+// one GPU share the array, so calls whose work overlaps on that GPU (other
+// streams, other threads) race.
 #include <hip/hip_runtime.h>
 
 #include <mutex>
