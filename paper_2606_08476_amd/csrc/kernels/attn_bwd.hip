@@ -24,14 +24,15 @@ __global__ __launch_bounds__(256, D == 64 ? 3 : 2) void attn_bwd_kernel(BwdParam
 
 // The non-deterministic backward pass: key tiles only, each also adding its
 // share of dQ into p.dq (zeroed beforehand) with atomics.
-// (kKeepNone: all the registers are taken. Kept values spilled 4 at head dim 128
-// and two heads per iteration, 16/8 heads over 32K tokens 1114 -> 1107 us; at 64
-// their lack leaves three waves per SIMD, 16/8 heads over 16K tokens with queries
-// scaled by 3, 462 -> 443 us.)
+// (kKeepNone where the registers are short. Kept values spilled 4 at head dim 128
+// and two heads per iteration, 16/8 heads over 32K tokens 1114 us against 1107; at
+// 64 their lack leaves three waves per SIMD, 16/8 heads over 16K tokens with
+// queries scaled by 3, 462 against 443. At 128 with one or four heads they fit:
+// 32/8 heads over 64K tokens 2421 us, without them 2450.)
 template <int D, int HPI>
 __global__ __launch_bounds__(256, 2) void attn_bwd_atomic_kernel(BwdParams p) {
   __shared__ __attribute__((aligned(16))) char smem[DkdvLds<D, true>::bytes];
-  dkdv_tile<D, true, HPI, kKeepNone>(p, blockIdx.x, smem);
+  dkdv_tile<D, true, HPI, D == 128 && HPI != 2 ? kKeepAll : kKeepNone>(p, blockIdx.x, smem);
 }
 
 // The whole backward pass in one launch: the first n_dkdv workgroups take
