@@ -359,8 +359,8 @@ int fc_bwd_preprocess(fc_view view, const void* o, const float* o_f32, const voi
  * dK/dV pass (writes dk_*, dv_*) and the query-major dQ pass (writes dq).
  * Key tiles seen by very many query tiles are split across workgroups that
  * write fp32 partials into ws, then summed in a fixed order, so dK/dV stay
- * reproducible. ws: device, >= the dkdv_bytes of fc_workspace_size; may be
- * NULL when that is 0 (no split key tile). fc_attn_bwd_pass likewise splits
+ * reproducible. ws: device, >= the dkdv_bytes of fc_workspace_size, or less
+ * as told there (NULL if no key tile is split). fc_attn_bwd_pass likewise splits
  * the key ranges of query tiles that would outlast the rest of the launch and
  * sums their partial dQ in a fixed order; fc_attn_bwd_dq, which takes no
  * workspace, never does. */
