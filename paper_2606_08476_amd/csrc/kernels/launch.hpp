@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <unistd.h>
 
 #include <mutex>
 
@@ -31,13 +32,16 @@ struct SlotGuard {
       if (const hipError_t e = hipSetDevice(dev_); e != hipSuccess) return e;
     const hipError_t e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (e != hipSuccess) ev = nullptr;
+    pid_ = getpid();
     if (dev_ != cur) (void)hipSetDevice(cur);
     return e;
   }
 
   hipError_t used(hipStream_t s) { return hipEventRecord(last_[dev_], s); }
 
+  // (no HIP call in a forked process that drops a view it inherited)
   ~SlotGuard() {
+    if (pid_ != getpid()) return;
     for (hipEvent_t ev : last_)
       if (ev) (void)hipEventDestroy(ev);
   }
@@ -46,6 +50,7 @@ struct SlotGuard {
   static constexpr int kDevices = 64;
   hipEvent_t last_[kDevices] = {};  // by device, made by the first use there
   int dev_ = 0;                     // the stream's device in wait()
+  pid_t pid_ = 0;                   // of the process that made the events
 };
 
 struct FwdParams {

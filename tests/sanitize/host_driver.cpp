@@ -14,6 +14,8 @@
 // "name cp plan rank_rule n_docs hq hkv d cu_0 ... cu_n" (plan: per_doc,
 // whole_lpt or hybrid; rank_rule: a rank number, "last" or "heaviest").
 #include <hip/hip_runtime.h>
+#include <sys/wait.h>
+#include <unistd.h>
 
 #include <algorithm>
 #include <array>
@@ -424,6 +426,16 @@ void slot_guard() {
     CHECK(g.wait(nullptr) == hipSuccess && g_waited == last[1] && g.used(nullptr) == hipSuccess);
     g_device = 0;
     CHECK(g_events == 2);
+    // a view inherited by a forked process and dropped there leaves the parent's
+    // events alone
+    const pid_t child = fork();
+    CHECK(child >= 0);
+    if (child == 0) {
+      g.~SlotGuard();
+      _exit(g_events == 2 ? 0 : 1);
+    }
+    int status = -1;
+    CHECK(waitpid(child, &status, 0) == child && WIFEXITED(status) && WEXITSTATUS(status) == 0);
   }
   CHECK(g_events == 0);
 }
